@@ -315,7 +315,8 @@ int qs_calc_inner_product(const qs_qureg *a, const qs_qureg *b, double *out_re, 
  * product of its members, each written densely on the block's qubits
  * (controls expanded, a gadget as cos(theta) 1 + i sin(theta) P, Sec.
  * "Pauli gadget").  Operators on more than fuse_k qubits stay single passes.
- * Blocks of 4-6 qubits on complex64 run as FP32 MFMA GEMMs.
+ * Blocks of 4-6 qubits (on at least 16 groups of amplitudes) run as GEMMs on
+ * the matrix cores, in FP32 for complex64 and FP64 for complex128.
  * 8 <= fuse_k <= 13 plans tile steps of at most 2^fuse_k amplitudes (a
  * coset of a GF(2) subspace of the index space holding the lowest qubits,
  * every target of a member gate and every gadget's X/Y flip mask): each
@@ -384,7 +385,7 @@ int qs_apply_circuit_passes(qs_qureg *q, qs_circuit *c, int first, int count);
 
 /* Describes pass `index` of the compiled circuit: kernel = 0 Pauli-gadget
  * pairs, 1 phase gadget (diagonal), 2 dense gate on vector FMAs, 3 dense
- * gate on FP32 MFMA, 4 tile step; num_targs / num_ctrls of a dense pass
+ * gate on the matrix cores, 4 tile step; num_targs / num_ctrls of a dense pass
  * (gadget: its Pauli count, 0; tile step: its dimension, 0); members =
  * recorded ops merged into the pass; phases = register layouts a tile step
  * moves through (1 for other passes).  Any out pointer may be NULL. */

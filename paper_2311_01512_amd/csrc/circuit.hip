@@ -334,8 +334,9 @@ int qs_circuit_compile(qs_circuit *c, int fuse_k, int precision)
             continue;
         }
         const int nt = (int)p.sorted_targs.size();
-        p.kernel = choose_dense_kernel(precision, nt);
-        const size_t b = dense_matrix_bytes(precision, nt, p.kernel);
+        const int rest = c->index_bits - nt - (int)p.ctrls.size();
+        p.kernel = choose_dense_kernel(precision, nt, rest >= 0 ? 1ULL << rest : 0);
+        const size_t b = dense_matrix_bytes(precision, nt);
         p.has_dev = b > 0;
         p.dev_offset = total;
         total += (b + 255) & ~size_t(255);
@@ -471,9 +472,7 @@ int qs_circuit_pass_info(const qs_circuit *c, int index, int *kernel, int *num_t
     } else {
         nt = (int)p.sorted_targs.size();
         nc = (int)p.ctrls.size();
-        const uint64_t groups = 1ULL << (c->index_bits - nt - nc);
-        const bool mfma = p.kernel == kDenseMfma && c->precision == QS_C64 && nt >= 4 && groups >= 16;
-        k = mfma ? 3 : 2;
+        k = p.kernel == kDenseMfma ? 3 : 2;
     }
     if (kernel) *kernel = k;
     if (num_targs) *num_targs = nt;

@@ -124,11 +124,11 @@ enum { kDenseVector = 0, kDenseMfma = 1 };
 std::vector<cd> permute_to_sorted(const std::vector<cd> &M, const std::vector<int> &targs,
                                   std::vector<int> &sorted_out);
 // Device bytes of a dense matrix in a kernel's layout (0: passed by value).
-size_t dense_matrix_bytes(int precision, int nt, int kernel);
+size_t dense_matrix_bytes(int precision, int nt);
 // Writes Ms (ascending target order, FP64) into out in the kernel's layout.
 void pack_dense(int precision, int nt, int kernel, const std::vector<cd> &Ms, void *out);
-// Kernel family used for an nt-target dense gate at a precision.
-int choose_dense_kernel(int precision, int nt);
+// Kernel family used for an nt-target dense gate on num_groups groups.
+int choose_dense_kernel(int precision, int nt, uint64_t num_groups);
 // Launches a dense gate whose matrix Ms is in ascending target order; dev is
 // its device copy in the kernel's layout, or null to stage it now.
 int launch_dense(qs_qureg *q, const std::vector<int> &ctrls, const std::vector<int> &sorted_targs,
@@ -143,7 +143,7 @@ std::vector<cd> superop_of_kraus(const std::vector<std::vector<cd>> &ks, int n);
 
 // ---- tuning knobs (tune.hip) ---------------------------------------------------
 
-// 1: dense gates of 4-6 targets on complex64 use MFMA, 0: vector FMAs.
+// 1: dense gates of 4-6 targets use MFMA, 0: vector FMAs.
 int mfma_preference();
 // Upper bound on the MFMA kernel's grid for a k-target gate.
 uint64_t mfma_block_cap(int k);

@@ -148,161 +148,168 @@ std::vector<cd> permute_to_sorted(const std::vector<cd> &M, const std::vector<in
     return out;
 }
 
-// ---- FP32 MFMA dense gate (complex64 state) -------------------------------------------
+// ---- dense gate of 4-6 targets on the matrix cores --------------------------------------
 //
-// The k-target gate as a real GEMM.  With G = Gr + i Gi (D x D, D = 2^k) and
-// a tile X of 16 groups (D x 16 complex), Y = G X is computed as
-//   [Yr; Yi] = [[Gr, -Gi], [Gi, Gr]] [Xr; Xi]
-// by v_mfma_f32_16x16x4f32: M = 2D output rows in 16-row blocks, K = 2D rows
-// of [Xr; Xi] in 4-row steps, N = 16 groups.  Lane L holds group L % 16;
-// for K-step s it holds row 4 s + L / 16 of [Xr; Xi] (the B operand), which
-// is the real (s < D/4) or imaginary part of one amplitude it loaded, and it
-// receives output rows 4 (L / 16) + i of each 16-row block (i = 0..3).  The
-// packed A operands (the big real matrix in MFMA lane order) sit in LDS.
+// The k-target gate as a real GEMM: with G = Gr + i Gi (D x D, D = 2^k) and a
+// tile X of 16 groups (D x 16 complex), Y = G X is
+//   Yr = Gr Xr + Gi (-Xi),  Yi = Gr Xi + Gi Xr
+// by v_mfma_f32_16x16x4f32 (complex64) or v_mfma_f64_16x16x4f64
+// (complex128): M = D output rows in 16-row blocks, K = D rows of X in 4-row
+// steps, N = 16 groups.  Operands: A holds row L % 16, column L / 16 of a
+// 16 x 4 block in lane L, B row L / 16, column L % 16 of a 4 x 16 block;
+// register i of the result is row 4 (L / 16) + i (FP32) or 4 i + L / 16
+// (FP64), column L % 16.  Lane L loads rows 4 s + L / 16 of group L % 16.  The
+// packed G has its rows placed so that the lane's results are rows
+// 4 (4 m + i) + L / 16 in both precisions: a lane writes the amplitudes that it
+// read, and one LDS read of its (Gr, Gi) pair feeds four MFMAs.
+//
+// A wave walks tiles tile + k num_waves with the next tile's loads issued
+// before the current tile's MFMAs (grid: mfma_block_cap).
+//
+// Bound: HBM (an in-place pass reaches about 6 TB/s) up to k = 5, the matrix
+// unit (large products reach 153 TFLOP/s in FP32, 72 in FP64) for k = 6.
+// Measured per gate on 1 GiB, targets spread / the lowest k (TB/s or TFLOP/s
+// in parentheses), with the vector kernel's time in complex128 and that of
+// an FP32 form with a 2D x 2D real matrix, whose lanes wrote other rows than
+// they read, in complex64:
+//   complex128  k = 4  424 / 744 -> 372 / 420 us (5.8 TB/s spread)
+//               k = 5  500 / 720 -> 421 / 421 us (5.1 TB/s)
+//               k = 6  2580 / 2659 -> 589 / 674 us (58 TFLOP/s)
+//   complex64   k = 4  383 / 616 -> 358 / 561 us (6.0 TB/s)
+//               k = 5  445 / 617 -> 411 / 567 us (5.2 TB/s)
+//               k = 6  637 / 768 -> 625 / 753 us (110 TFLOP/s)
+// Two tiles per wave and step were no faster, nor were lane rows on other
+// target bits than the two lowest.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int K>
-__global__ __launch_bounds__(256) void k_dense_mfma(float2 *__restrict__ a, uint64_t num_tiles, InsertPlan plan,
-                                                     uint64_t ctrl_mask, TargBits tb,
-                                                     const f32x4 *__restrict__ apack)
+template <typename R> struct mfma_acc;
+template <> struct mfma_acc<float> { using type = f32x4; };
+template <> struct mfma_acc<double> { using type = f64x4; };
+
+__device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 c)
 {
-    constexpr int D = 1 << K;
-    constexpr int KS = 2 * D / 4;    // K-steps
-    constexpr int MB = 2 * D / 16;   // 16-row output blocks
-    constexpr int NA = MB * KS / 4;  // float4 A-operand packs per lane
-    extern __shared__ f32x4 lds_a[];
-    for (int i = threadIdx.x; i < NA * 64; i += blockDim.x) lds_a[i] = apack[i];
-    __syncthreads();
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
+__device__ __forceinline__ f64x4 mfma_16x16x4(double a, double b, f64x4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+template <typename R, int K>
+__global__ __launch_bounds__(256) void k_dense_mfma(C2<R> *__restrict__ a, uint64_t num_tiles, InsertPlan plan,
+                                                     uint64_t ctrl_mask, TargBits tb, const C2<R> *__restrict__ gpack)
+{
+    using Acc = typename mfma_acc<R>::type;
+    constexpr int D = 1 << K;
+    constexpr int KS = D / 4;     // K-steps, and amplitudes per lane
+    constexpr int MB = D / 16;    // 16-row output blocks
+    extern __shared__ unsigned char lds_raw[];
+    C2<R> *lds_g = reinterpret_cast<C2<R> *>(lds_raw);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 15, rq = lane >> 4;
-    // input row 4 s + rq: target bits 0-1 from rq (per lane), bits >= 2 from s
-    const uint64_t off_in = ((rq & 1) ? tb.b[0] : 0) | ((rq & 2) ? tb.b[1] : 0);
-    // output row 16 m + 4 rq + i: target bits 2-3 from rq (per lane)
-    const uint64_t off_out = ((rq & 1) ? tb.b[2] : 0) | ((rq & 2) ? tb.b[3] : 0);
-    const uint64_t num_waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
-
-    // input offsets of this lane's D/4 amplitudes within a group
-    uint64_t in_off[D / 4];
-#pragma unroll
-    for (int s = 0; s < D / 4; s++) {
-        uint64_t o = off_in;
+    const uint64_t off = ctrl_mask | ((rq & 1) ? tb.b[0] : 0) | ((rq & 2) ? tb.b[1] : 0);
+    // target bits >= 2 of the lane's amplitude s: the same for every lane
+    auto step_off = [&](int s) {
+        uint64_t o = 0;
 #pragma unroll
         for (int p = 2; p < K; p++)
             if ((s >> (p - 2)) & 1) o |= tb.b[p];
-        in_off[s] = o;
-    }
+        return o;
+    };
+    const uint64_t num_waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
     uint64_t tile = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+    // the first tile's amplitudes and G are in flight together
+    C2<R> x[KS];
+    uint64_t base = insert_zeros(tile * 16 + col, plan) | off;
+#pragma unroll
+    for (int s = 0; s < KS; s++) x[s] = tile < num_tiles ? a[base | step_off(s)] : mk<R>(R(0), R(0));
+    for (int i = threadIdx.x; i < D * D; i += blockDim.x) lds_g[i] = gpack[i];
+    __syncthreads();
     if (tile >= num_tiles) return;
-    // software pipeline: the next tile's amplitudes are loaded while this
-    // tile's MFMAs run (a wave walks tiles tile + k num_waves); the first
-    // tile is waited for before the loop, so the loop never waits on stores
-    float2 x[D / 4];
-    {
-        const uint64_t b0 = insert_zeros(tile * 16 + col, plan) | ctrl_mask;
-#pragma unroll
-        for (int s = 0; s < D / 4; s++) x[s] = a[b0 | in_off[s]];
-#pragma unroll
-        for (int s = 0; s < D / 4; s++) asm volatile("" ::"v"(x[s].x), "v"(x[s].y));
-    }
-    for (; tile < num_tiles; tile += num_waves) {
+    for (;;) {
         // keep the LDS operand reads inside the loop (no hoisting into registers)
         asm volatile("" ::: "memory");
-        const uint64_t base = insert_zeros(tile * 16 + col, plan) | ctrl_mask;
-        const bool more = tile + num_waves < num_tiles;
-        float2 nx[D / 4];
+        const uint64_t next = tile + num_waves;
+        const bool more = next < num_tiles;
+        C2<R> nx[KS];
+        uint64_t nb = 0;
+#pragma unroll
+        for (int s = 0; s < KS; s++) nx[s] = mk<R>(R(0), R(0));
         if (more) {
-            const uint64_t nb = insert_zeros((tile + num_waves) * 16 + col, plan) | ctrl_mask;
+            nb = insert_zeros(next * 16 + col, plan) | off;
 #pragma unroll
-            for (int s = 0; s < D / 4; s++) nx[s] = a[nb | in_off[s]];
+            for (int s = 0; s < KS; s++) nx[s] = a[nb | step_off(s)];
         }
-        f32x4 acc[MB];
 #pragma unroll
-        for (int m = 0; m < MB; m++) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MB; m++) {
+            Acc yr = {R(0), R(0), R(0), R(0)}, yi = {R(0), R(0), R(0), R(0)};
 #pragma unroll
-        for (int kq = 0; kq < KS / 4; kq++) {
-#pragma unroll
-            for (int m = 0; m < MB; m++) {
-                const f32x4 av = lds_a[(m * (KS / 4) + kq) * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int ks = 4 * kq + r;
-                    const float bv = ks < D / 4 ? x[ks].x : x[ks - D / 4].y;
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv, acc[m], 0, 0, 0);
-                }
+            for (int s = 0; s < KS; s++) {
+                const C2<R> g = lds_g[(m * KS + s) * 64 + lane];
+                yr = mfma_16x16x4(g.x, x[s].x, yr);
+                yi = mfma_16x16x4(g.x, x[s].y, yi);
+                yr = mfma_16x16x4(g.y, -x[s].y, yr);
+                yi = mfma_16x16x4(g.y, x[s].x, yi);
             }
+#pragma unroll
+            for (int i = 0; i < 4; i++) a[base | step_off(4 * m + i)] = mk<R>(yr[i], yi[i]);
         }
+        if (!more) return;
 #pragma unroll
-        for (int m = 0; m < D / 16; m++) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                uint64_t o = off_out | ((i & 1) ? tb.b[0] : 0) | ((i & 2) ? tb.b[1] : 0);
-#pragma unroll
-                for (int p = 4; p < K; p++)
-                    if ((m >> (p - 4)) & 1) o |= tb.b[p];
-                a[base | o] = make_float2(acc[m][i], acc[m + D / 16][i]);
-            }
-        }
-        if (more) {
-#pragma unroll
-            for (int s = 0; s < D / 4; s++) x[s] = nx[s];
-        }
+        for (int s = 0; s < KS; s++) x[s] = nx[s];
+        base = nb;
+        tile = next;
     }
 }
 
-// Packs a D x D complex matrix (sorted target order) into the A-operand
-// order of k_dense_mfma: element r of float4 number (m * KS/4 + kq) * 64 + L
-// is B[16 m + L % 16][4 (4 kq + r) + L / 16] of the real matrix
-// B = [[Gr, -Gi], [Gi, Gr]].
-static void pack_mfma(const std::vector<cd> &Ms, int k, float *out)
+// Packs G (sorted target order) into the operand order of k_dense_mfma:
+// entry (m KS + s) * 64 + L is G[16 m + r][4 s + L / 16], where r is the row
+// whose result the matrix unit puts where row L % 16 of the block belongs.
+template <typename R>
+static void pack_mfma(const std::vector<cd> &Ms, int k, C2<R> *out)
 {
-    const int D = 1 << k, KS = 2 * D / 4, MB = 2 * D / 16;
-    auto big = [&](int row, int c) -> double {
-        const cd g = Ms[(size_t)(row % D) * D + (c % D)];
-        const bool rim = row >= D, cim = c >= D;
-        if (!rim && !cim) return g.real();
-        if (!rim && cim) return -g.imag();
-        if (rim && !cim) return g.imag();
-        return g.real();
-    };
+    const int D = 1 << k, KS = D / 4, MB = D / 16;
     for (int m = 0; m < MB; m++)
-        for (int kq = 0; kq < KS / 4; kq++)
-            for (int L = 0; L < 64; L++)
-                for (int r = 0; r < 4; r++)
-                    out[(((size_t)m * (KS / 4) + kq) * 64 + L) * 4 + r] =
-                        (float)big(16 * m + (L % 16), 4 * (4 * kq + r) + L / 16);
+        for (int s = 0; s < KS; s++)
+            for (int L = 0; L < 64; L++) {
+                const int j = L % 16, r = same_type<R, float>::value ? 4 * (j % 4) + j / 4 : j;
+                const cd g = Ms[(size_t)(16 * m + r) * D + 4 * s + L / 16];
+                out[((size_t)m * KS + s) * 64 + L] = C2<R>{(R)g.real(), (R)g.imag()};
+            }
 }
 
 // ---- dense-gate launch interface ------------------------------------------------------------
 
-size_t dense_matrix_bytes(int precision, int nt, int kernel)
+size_t dense_matrix_bytes(int precision, int nt)
 {
     const size_t D = (size_t)1 << nt;
-    if (kernel == kDenseMfma) return 4 * D * D * sizeof(float);
     if (nt <= 2) return 0;                               // passed by value
     return D * D * (precision == QS_C64 ? sizeof(float2) : sizeof(double2));
 }
 
-void pack_dense(int precision, int nt, int kernel, const std::vector<cd> &Ms, void *out)
+template <typename R>
+static void pack_dense_r(int nt, int kernel, const std::vector<cd> &Ms, C2<R> *out)
 {
-    const size_t D = (size_t)1 << nt;
     if (kernel == kDenseMfma) {
-        pack_mfma(Ms, nt, (float *)out);
-    } else if (precision == QS_C64) {
-        float2 *o = (float2 *)out;
-        for (size_t i = 0; i < D * D; i++) o[i] = make_float2((float)Ms[i].real(), (float)Ms[i].imag());
-    } else {
-        double2 *o = (double2 *)out;
-        for (size_t i = 0; i < D * D; i++) o[i] = make_double2(Ms[i].real(), Ms[i].imag());
+        pack_mfma<R>(Ms, nt, out);
+        return;
     }
+    const size_t D = (size_t)1 << nt;
+    for (size_t i = 0; i < D * D; i++) out[i] = C2<R>{(R)Ms[i].real(), (R)Ms[i].imag()};
 }
 
-int choose_dense_kernel(int precision, int nt)
+void pack_dense(int precision, int nt, int kernel, const std::vector<cd> &Ms, void *out)
 {
-    const int pref = mfma_preference();
-    if (precision != QS_C64 || nt < 4 || nt > 6) return kDenseVector;
-    if (pref == 0) return kDenseVector;
-    return kDenseMfma;
+    if (precision == QS_C64) pack_dense_r<float>(nt, kernel, Ms, (float2 *)out);
+    else pack_dense_r<double>(nt, kernel, Ms, (double2 *)out);
+}
+
+int choose_dense_kernel(int, int nt, uint64_t num_groups)
+{
+    // a wavefront takes 16 groups
+    return nt >= 4 && nt <= 6 && num_groups >= 16 && mfma_preference() ? kDenseMfma : kDenseVector;
 }
 
 template <typename R, int NT>
@@ -331,28 +338,38 @@ static int launch_vector(qs_qureg *q, uint64_t num_groups, const InsertPlan &pla
     return QS_OK;
 }
 
-template <int K>
+template <typename R, int K>
 static int launch_mfma(qs_qureg *q, uint64_t num_groups, const InsertPlan &plan, uint64_t ctrl_mask,
                        const TargBits &tb, const std::vector<cd> &Ms, const void *dev)
 {
-    constexpr int D = 1 << K;
-    const size_t bytes = 4 * (size_t)D * D * sizeof(float);
+    constexpr size_t bytes = (sizeof(C2<R>) << (2 * K));
     if (!dev) {
-        std::vector<float> hm(4 * D * D);
-        pack_mfma(Ms, K, hm.data());
+        std::vector<C2<R>> hm((size_t)1 << (2 * K));
+        pack_mfma<R>(Ms, K, hm.data());
         int rc = stage_matrix(q, hm.data(), bytes, &dev);
         if (rc != QS_OK) return rc;
     }
-    const uint64_t tiles = num_groups / 16;   // num_groups is a multiple of 16 (checked by the caller)
+    const uint64_t tiles = num_groups / 16;   // num_groups is a multiple of 16 (choose_dense_kernel)
     const uint64_t waves_per_block = 4;
     uint64_t blocks = (tiles + waves_per_block - 1) / waves_per_block;
     uint64_t cap = mfma_block_cap(K);
     if (cap > 0xFFFFFFFFull / 256) cap = 0xFFFFFFFFull / 256;   // 32-bit dispatch size in work-items
     if (blocks > cap) blocks = cap;
-    hipLaunchKernelGGL((k_dense_mfma<K>), dim3((unsigned)blocks), dim3(256), bytes, q->stream, (float2 *)q->amps,
-                       tiles, plan, ctrl_mask, tb, (const f32x4 *)dev);
+    hipLaunchKernelGGL((k_dense_mfma<R, K>), dim3((unsigned)blocks), dim3(256), bytes, q->stream, (C2<R> *)q->amps,
+                       tiles, plan, ctrl_mask, tb, (const C2<R> *)dev);
     QS_LAUNCH_CHECK();
     return QS_OK;
+}
+
+template <typename R>
+static int launch_mfma_r(qs_qureg *q, int nt, uint64_t num_groups, const InsertPlan &plan, uint64_t ctrl_mask,
+                         const TargBits &tb, const std::vector<cd> &Ms, const void *dev)
+{
+    switch (nt) {
+    case 4: return launch_mfma<R, 4>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
+    case 5: return launch_mfma<R, 5>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
+    default: return launch_mfma<R, 6>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
+    }
 }
 
 template <typename R>
@@ -385,17 +402,13 @@ int launch_dense(qs_qureg *q, const std::vector<int> &ctrls, const std::vector<i
     TargBits tb{};
     for (int p = 0; p < nt; p++) tb.b[p] = 1ULL << sorted_targs[p];
     const uint64_t num_groups = 1ULL << (q->index_bits - nc - nt);
-    if (kernel == kDenseMfma && (q->precision != QS_C64 || nt < 4 || num_groups < 16)) {
+    if (kernel == kDenseMfma && (nt < 4 || num_groups < 16)) {
         kernel = kDenseVector;
         dev = nullptr;   // a device copy in the MFMA layout does not fit the vector kernel
     }
-    if (kernel == kDenseMfma) {
-        switch (nt) {
-        case 4: return launch_mfma<4>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
-        case 5: return launch_mfma<5>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
-        default: return launch_mfma<6>(q, num_groups, plan, ctrl_mask, tb, Ms, dev);
-        }
-    }
+    if (kernel == kDenseMfma)
+        return q->precision == QS_C64 ? launch_mfma_r<float>(q, nt, num_groups, plan, ctrl_mask, tb, Ms, dev)
+                                      : launch_mfma_r<double>(q, nt, num_groups, plan, ctrl_mask, tb, Ms, dev);
     return q->precision == QS_C64 ? launch_vector_r<float>(q, nt, num_groups, plan, ctrl_mask, tb, Ms, dev)
                                   : launch_vector_r<double>(q, nt, num_groups, plan, ctrl_mask, tb, Ms, dev);
 }
@@ -407,8 +420,9 @@ int apply_raw_gate(qs_qureg *q, const std::vector<int> &ctrls, const std::vector
 {
     std::vector<int> sorted;
     std::vector<cd> Ms = permute_to_sorted(M, targs, sorted);
-    const int nt = (int)targs.size();
-    return launch_dense(q, ctrls, sorted, Ms, nullptr, choose_dense_kernel(q->precision, nt));
+    const int nt = (int)targs.size(), rest = q->index_bits - nt - (int)ctrls.size();
+    return launch_dense(q, ctrls, sorted, Ms, nullptr,
+                        choose_dense_kernel(q->precision, nt, rest >= 0 ? 1ULL << rest : 0));
 }
 
 // Pauli gadget on the raw array (index_bits qubits).

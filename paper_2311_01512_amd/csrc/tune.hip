@@ -1,8 +1,8 @@
 // Launch-policy knobs and the fusion-width autotuner.
 //
 // Knobs default to values measured on MI355X and can be overridden from the
-// environment: QS_DENSE_KERNEL=vector|mfma (dense gates of 4-6 targets on
-// complex64), QS_MFMA_BLOCKS=<max blocks of the MFMA kernel>,
+// environment: QS_DENSE_KERNEL=vector|mfma (dense gates of 4-6 targets),
+// QS_MFMA_BLOCKS=<max blocks of the MFMA kernel>,
 // QS_TILE_LOW=<lowest qubits every tile step holds>,
 // QS_STEP_WAVES=<waves per SIMD the specialised tile steps are compiled for>,
 // QS_TILE_CHUNK=<tiles per block of the chunk policy; unset: as many blocks
@@ -41,12 +41,13 @@ uint64_t mfma_block_cap(int k)
         return (uint64_t)0;
     }();
     if (forced) return forced;
-    // measured on MI355X at 28 qubits: one tile per wave is best for 4
-    // targets; 5 and 6 targets do better with waves that walk several tiles
-    // (the 16-64 KiB A operand is staged into LDS once per block)
-    if (k >= 6) return 2048;
-    if (k == 5) return 8192;
-    return (uint64_t)1 << 30;
+    // 4 targets: one tile per wave (on 1 GiB 358 us in complex64 and 372 us
+    // in complex128, against 400 and 384 us with two blocks per CU).  5 and 6
+    // targets: two blocks per CU, whose waves walk many tiles, so that the
+    // 8-64 KiB matrix is staged into LDS once per block (5 targets: 411 and
+    // 421 us against 501 and 477 us with one tile per wave; 6 targets: 625
+    // and 589 us against 803 and 839 us).
+    return k >= 5 ? 512 : (uint64_t)1 << 30;
 }
 
 int step_waves_per_eu(bool f32)
