@@ -435,12 +435,16 @@ int qs_circuit_set_params(qs_circuit *c, const double *params, int num_params);
  * Energy E = <psi|H|psi> of H = sum_n coeffs[n] P_n (paulis: num_terms
  * strings of N codes, term-major) after the circuit, and dE/dparams[p] for
  * every parameter, by the adjoint method: psi (holding the initial state)
- * is run through the circuit one operator per pass, lambda = H psi (lam: a
- * statevector qureg of the same size, precision and stream, overwritten),
- * then for each operator from last to first dE/dtheta_p += -2 scale
- * Im <lambda|P|psi> for a parametrised gadget and psi, lambda <-
- * U^dag psi, U^dag lambda.  On return psi holds the initial state again (up
- * to rounding).  grads receives num_params values; energy one.  Sums in FP64.
+ * is run through the circuit, lambda = H psi (lam: a statevector qureg of the
+ * same size, precision and stream, overwritten), then for each operator from
+ * last to first dE/dtheta_p += -2 scale Im <lambda|P|psi> for a parametrised
+ * gadget and psi, lambda <- U^dag psi, U^dag lambda.  On return psi holds the
+ * initial state again (up to rounding).  grads receives num_params values;
+ * energy one.  Sums in FP64.  On 9 or more qubits, when every matrix is
+ * unitary to the precision's rounding, both directions run as tile steps
+ * (see qs_circuit_compile; operators that fit no tile as passes of their own);
+ * their plan and its device buffers (at most about 64 MiB of partial sums)
+ * stay with the circuit for its next gradient.
  */
 int qs_circuit_adjoint_gradient(qs_circuit *c, qs_qureg *psi, qs_qureg *lam, const int *paulis,
                                 const double *coeffs, int num_terms, int num_params, double *energy,

@@ -8,10 +8,15 @@
 // is a parametrised gadget, dE/dtheta_p += 2 Re(i scale <lambda|P|psi>) =
 // -2 scale Im <lambda|P|psi> (psi is then the state after U_k, lambda the
 // back-propagated H psi); then psi <- U_k^dag psi and lambda <- U_k^dag lambda.
+//
+// On 9 qubits or more, with unitary gates, both directions run as tile steps
+// (adjoint_tiles); otherwise one operator per pass.
 #include "circuit.hpp"
 
 #include <algorithm>
 #include <cmath>
+#include <memory>
+#include <mutex>
 
 namespace qs {
 
@@ -174,16 +179,262 @@ static int apply_op(qs_qureg *q, const CircOp &op, bool adjoint)
     return apply_raw_gate(q, op.ctrls, op.targs, adjoint_of(op.M, (size_t)1 << op.targs.size()));
 }
 
-template <typename R>
-static int adjoint_sweep(const qs_circuit *c, qs_qureg *psi, qs_qureg *lam, const int *codes, const double *coeffs,
-                         int T, int num_params, double *energy, double *grads)
+// ---- the sweep as tile steps -------------------------------------------------------
+//
+// One operator per pass reads and writes a state for each of the sweep's
+// three applications, and each gradient reads both states and waits for its
+// sum.  As tile steps the forward circuit is one pass over psi per step, and
+// the way back one pass over psi and lambda per step, in which the step's
+// gadgets also form their gradients (k_tile_adjoint); the sums of all of them
+// come back in one copy.
+//
+// Inside a step operators may trade places with operators they commute with.
+// That leaves each gradient alone when the gates it moved across are unitary
+// (<V^dag lambda|P|V^dag psi> = <lambda|P|psi> for unitary V that commutes
+// with P), so circuits with other matrices keep the operator-by-operator sweep.
+
+struct AdjointPlan {
+    size_t num_ops = 0;
+    int precision = -1, device = -1, num_qubits = 0;
+    bool tiles = false;                 // false: the operator-by-operator sweep
+    std::vector<TileStep> steps;
+    std::vector<CircOp> rev;            // adjoint of every operator
+    int num_grads = 0;                  // parametrised gadgets
+    unsigned blocks = 0;                // grid of the steps of the way back
+    // device tables of all steps (forward, then backward) and their pinned copy
+    unsigned char *dev = nullptr, *host = nullptr;
+    size_t bytes = 0;
+    double *gpart = nullptr;            // num_grads rows of `blocks` partial sums
+    double *d_out = nullptr, *h_out = nullptr;   // energy (re, im), then one sum per gradient
+
+    AdjointPlan() = default;
+    AdjointPlan(const AdjointPlan &) = delete;
+    ~AdjointPlan()
+    {
+        release_tables();
+        if (gpart) (void)hipFree(gpart);
+        if (d_out) (void)hipFree(d_out);
+        if (h_out) (void)hipHostFree(h_out);
+    }
+    void release_tables()
+    {
+        if (dev) (void)hipFree(dev);
+        if (host) (void)hipHostFree(host);
+        dev = host = nullptr;
+        bytes = 0;
+    }
+    // At least n bytes of tables; earlier contents are lost when they grow.
+    int reserve_tables(size_t n)
+    {
+        if (bytes >= n) return QS_OK;
+        release_tables();
+        if (hipMalloc(&dev, n) != hipSuccess || hipHostMalloc(&host, n, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(QS_E_ALLOC, "allocation of the adjoint sweep's tables failed");
+        }
+        bytes = n;
+        return QS_OK;
+    }
+};
+
+// The plan's buffers belong to the states' device.
+struct DeviceGuard {
+    int before = -1;
+    explicit DeviceGuard(int device)
+    {
+        if (hipGetDevice(&before) != hipSuccess || before == device || hipSetDevice(device) != hipSuccess) before = -1;
+    }
+    ~DeviceGuard()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
+// A step's gradients share the block's LDS with its tile.
+constexpr int kStepGrads = 32;
+// Most doubles of gradient partials (64 MiB).
+constexpr size_t kGradPartials = (size_t)1 << 23;
+
+static bool is_unitary(const CircOp &op, double tol)
 {
-    for (int p = 0; p < num_params; p++) grads[p] = 0.0;
-    for (const auto &op : c->ops) {
-        int rc = apply_op(psi, op, false);
+    const size_t d = (size_t)1 << op.targs.size();
+    for (size_t r = 0; r < d; r++)
+        for (size_t c = 0; c <= r; c++) {
+            cd z = r == c ? cd(-1, 0) : cd(0, 0);
+            for (size_t k = 0; k < d; k++) z += op.M[r * d + k] * std::conj(op.M[c * d + k]);
+            if (!(std::abs(z) <= tol)) return false;
+        }
+    return true;
+}
+
+// Tiles of 2^12 (complex64) or 2^11 (complex128) amplitudes: both states of a
+// tile take 32 KiB of LDS in turn.
+static int adjoint_tile_dim(int precision, int num_qubits)
+{
+    return std::min({num_qubits, precision == QS_C64 ? 12 : 11, tile_dim_limit(precision)});
+}
+
+static int build_adjoint_plan(AdjointPlan &pl, const qs_circuit *c, const qs_qureg *psi)
+{
+    pl.num_ops = c->ops.size();
+    pl.precision = psi->precision;
+    pl.device = psi->device;
+    pl.num_qubits = c->num_qubits;
+    // the gradients' wave sums need whole wavefronts: tiles of 2^9 or more
+    const int T = adjoint_tile_dim(pl.precision, c->num_qubits);
+    if (T < kRegBits + 6) return QS_OK;
+    // rounding of a matrix given in the state's precision is let through
+    const double tol = pl.precision == QS_C64 ? 1e-6 : 1e-13;
+    for (const auto &op : c->ops)
+        if (!op.gadget && !is_unitary(op, tol)) return QS_OK;
+    pl.steps = group_tile_steps(c->ops, c->num_qubits, T, pl.precision, -1, kStepGrads);
+    pl.rev = c->ops;
+    for (auto &op : pl.rev) {
+        if (!op.gadget) op.M = adjoint_of(op.M, (size_t)1 << op.targs.size());
+        else if (op.param >= 0) pl.num_grads++;
+    }
+    const uint64_t tiles = 1ULL << (c->num_qubits - T);
+    pl.blocks = (unsigned)std::min<uint64_t>(tiles, 2048);
+    while (pl.blocks > 256 && (size_t)pl.blocks * pl.num_grads > kGradPartials) pl.blocks /= 2;
+    const size_t out = sizeof(double) * (2 + (size_t)pl.num_grads);
+    if (hipMalloc(&pl.gpart, sizeof(double) * std::max<size_t>(1, (size_t)pl.blocks * pl.num_grads)) != hipSuccess ||
+        hipMalloc(&pl.d_out, out) != hipSuccess || hipHostMalloc(&pl.h_out, out, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(QS_E_ALLOC, "allocation of the adjoint sweep's sums failed");
+    }
+    pl.tiles = true;
+    return QS_OK;
+}
+
+// Encodes one direction's steps, in application order, with the angles of
+// `ops` (the circuit's operators, or their adjoints last first).
+static std::vector<Pass> encode_direction(const AdjointPlan &pl, const std::vector<CircOp> &ops, bool back)
+{
+    std::vector<Pass> out(pl.steps.size());
+    const bool mfma = pl.precision == QS_C64;
+    for (size_t k = 0; k < pl.steps.size(); k++) {
+        const TileStep &st = pl.steps[back ? pl.steps.size() - 1 - k : k];
+        if (st.single >= 0) continue;
+        std::vector<const CircOp *> members;
+        for (int j : st.members) members.push_back(&ops[j]);
+        if (back) std::reverse(members.begin(), members.end());
+        encode_step(out[k], st.span, members, mfma, back);
+    }
+    return out;
+}
+
+// Gives the passes their places in the plan's tables from `offset` on;
+// returns the end.
+static size_t place_tables(const AdjointPlan &pl, std::vector<Pass> &passes, size_t offset)
+{
+    for (Pass &p : passes) {
+        if (!p.tile) continue;
+        p.dev_offset = offset;
+        offset += (tile_pass_bytes(p, pl.precision) + 255) & ~size_t(255);
+    }
+    return offset;
+}
+
+// Copies the passes' tables to the device, ordered on the stream.
+static int upload_tables(AdjointPlan &pl, const std::vector<Pass> &passes, size_t begin, size_t end, hipStream_t stream)
+{
+    for (const Pass &p : passes)
+        if (p.tile) pack_tile_pass(p, pl.precision, pl.host + p.dev_offset);
+    if (end > begin) QS_HIP(hipMemcpyAsync(pl.dev + begin, pl.host + begin, end - begin, hipMemcpyHostToDevice, stream));
+    return QS_OK;
+}
+
+template <typename R>
+static int adjoint_tiles(AdjointPlan &pl, const qs_circuit *c, qs_qureg *psi, qs_qureg *lam, const int *codes,
+                         const double *coeffs, int T, int num_params, double *energy, double *grads)
+{
+    for (size_t k = 0; k < c->ops.size(); k++)
+        if (c->ops[k].gadget) pl.rev[k].theta = -c->ops[k].theta;
+    std::vector<Pass> fwd = encode_direction(pl, c->ops, false);
+    const size_t mid = place_tables(pl, fwd, 0);
+    // room for the way back as well: its tables hold the same operators (and
+    // at most one scaling operator more per step)
+    int rc = pl.reserve_tables(2 * mid + 1024 * pl.steps.size() + 4096);
+    if (rc == QS_OK) rc = upload_tables(pl, fwd, 0, mid, psi->stream);
+    if (rc != QS_OK) return rc;
+    const size_t S = pl.steps.size();
+    for (size_t k = 0; k < S; k++) {
+        const TileStep &st = pl.steps[k];
+        rc = st.single >= 0 ? apply_op(psi, c->ops[st.single], false) : launch_tile_pass(psi, fwd[k], pl.dev + fwd[k].dev_offset);
         if (rc != QS_OK) return rc;
     }
-    int rc = apply_observable<R>(lam, psi, codes, coeffs, T);
+    rc = apply_observable<R>(lam, psi, codes, coeffs, T);
+    if (rc == QS_OK) rc = queue_inner_product(psi, lam, pl.d_out);
+    if (rc != QS_OK) return rc;
+    // encoded while the device runs the above
+    std::vector<Pass> back = encode_direction(pl, pl.rev, true);
+    const size_t end = place_tables(pl, back, mid);
+    if (end > pl.bytes) {
+        // fused differently, they can be larger: wait for the forward steps
+        QS_HIP(hipStreamSynchronize(psi->stream));
+        rc = pl.reserve_tables(end);
+    }
+    if (rc == QS_OK) rc = upload_tables(pl, back, mid, end, psi->stream);
+    if (rc != QS_OK) return rc;
+    size_t row = 0;
+    for (size_t k = 0; k < S; k++) {
+        const TileStep &st = pl.steps[S - 1 - k];
+        if (st.single >= 0) {
+            rc = apply_op(psi, c->ops[st.single], true);
+            if (rc == QS_OK) rc = apply_op(lam, c->ops[st.single], true);
+        } else {
+            rc = launch_adjoint_pass(psi, lam, back[k], pl.dev + back[k].dev_offset, pl.gpart + row * pl.blocks, pl.blocks);
+            row += back[k].grads.size();
+        }
+        if (rc != QS_OK) return rc;
+    }
+    rc = queue_row_sums(psi->stream, pl.gpart, (int)row, (int)pl.blocks, pl.d_out + 2);
+    if (rc != QS_OK) return rc;
+    QS_HIP(hipMemcpyAsync(pl.h_out, pl.d_out, sizeof(double) * (2 + row), hipMemcpyDeviceToHost, psi->stream));
+    QS_HIP(hipStreamSynchronize(psi->stream));
+    *energy = pl.h_out[0];
+    for (int p = 0; p < num_params; p++) grads[p] = 0.0;
+    const double *sum = pl.h_out + 2;
+    for (const Pass &p : back)
+        for (const GradRef &g : p.grads) grads[g.param] += g.weight * *sum++;
+    return QS_OK;
+}
+
+template <typename R>
+static int adjoint_sweep(qs_circuit *c, qs_qureg *psi, qs_qureg *lam, const int *codes, const double *coeffs,
+                         int T, int num_params, double *energy, double *grads)
+{
+    const DeviceGuard guard(psi->device);
+    std::shared_ptr<AdjointPlan> pl;
+    {
+        std::lock_guard<std::mutex> lock(c->adjoint_mu);
+        pl.swap(c->adjoint);
+    }
+    int rc = QS_OK;
+    // operators are only ever appended: the same count, the same structure
+    if (!pl || pl->num_ops != c->ops.size() || pl->precision != psi->precision || pl->device != psi->device) {
+        pl = std::make_shared<AdjointPlan>();
+        rc = build_adjoint_plan(*pl, c, psi);
+        if (rc != QS_OK) return rc;
+    }
+    if (pl->tiles) {
+        rc = adjoint_tiles<R>(*pl, c, psi, lam, codes, coeffs, T, num_params, energy, grads);
+        if (rc != QS_OK) {
+            (void)hipStreamSynchronize(psi->stream);   // queued steps read the plan's tables
+            return rc;
+        }
+    }
+    {
+        std::lock_guard<std::mutex> lock(c->adjoint_mu);
+        c->adjoint = pl;
+    }
+    if (pl->tiles) return QS_OK;
+    for (int p = 0; p < num_params; p++) grads[p] = 0.0;
+    for (const auto &op : c->ops) {
+        rc = apply_op(psi, op, false);
+        if (rc != QS_OK) return rc;
+    }
+    rc = apply_observable<R>(lam, psi, codes, coeffs, T);
     if (rc != QS_OK) return rc;
     double re = 0.0, im = 0.0;
     rc = qs_calc_inner_product(psi, lam, &re, &im);

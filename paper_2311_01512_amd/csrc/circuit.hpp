@@ -4,7 +4,42 @@
 
 #include "common.hpp"
 
+#include <map>
+#include <memory>
+#include <mutex>
+
 namespace qs {
+
+// ---- GF(2) reduced echelon basis ----------------------------------------------------
+
+struct Echelon {
+    std::map<int, uint64_t> by_pivot;   // pivot bit -> vector (pivot = highest set bit)
+
+    uint64_t reduce(uint64_t x) const
+    {
+        for (auto it = by_pivot.rbegin(); it != by_pivot.rend(); ++it)
+            if ((x >> it->first) & 1ULL) x ^= it->second;
+        return x;
+    }
+    // Adds x; keeps every pivot bit set in exactly one vector.
+    bool add(uint64_t x)
+    {
+        x = reduce(x);
+        if (!x) return false;
+        const int p = 63 - __builtin_clzll(x);
+        for (auto &kv : by_pivot)
+            if ((kv.second >> p) & 1ULL) kv.second ^= x;
+        by_pivot[p] = x;
+        return true;
+    }
+    int dim() const { return (int)by_pivot.size(); }
+    int dim_with(const std::vector<uint64_t> &xs) const
+    {
+        Echelon e = *this;
+        for (uint64_t x : xs) e.add(x);
+        return e.dim();
+    }
+};
 
 struct CircOp {
     bool gadget;
@@ -67,6 +102,14 @@ inline bool ops_commute(const OpMasks &a, const OpMasks &b)
     return (a.t & (b.t | b.c)) == 0 && (b.t & a.c) == 0;
 }
 
+// A gradient that an adjoint tile step sums: dE/dparam gets weight times the
+// sum of the gadget at operator `rop`.
+struct GradRef {
+    int param;
+    double weight;
+    size_t rop;
+};
+
 struct Pass {
     bool gadget;
     std::vector<int> ctrls, sorted_targs;
@@ -85,6 +128,7 @@ struct Pass {
     std::vector<RPhase> phases;
     std::vector<ROp> rops;
     std::vector<cd> tmats;            // dense matrices of the step, concatenated
+    std::vector<GradRef> grads;       // adjoint steps: the sums, in operator order
     // kernel specialised for this step at run time (jit.hip), or null
     void *jit_fn = nullptr;
     unsigned jit_grid = 0;            // its resident-block grid
@@ -97,6 +141,21 @@ int tile_dim_limit(int precision);
 // Plans the circuit as LDS tile steps of at most T dimensions (operators
 // that do not fit a tile become single passes) into c->passes.
 void plan_tiles(qs_circuit *c, int T, int precision);
+// One tile step of a plan: its subspace and member operators, or one operator
+// that runs as a pass of its own.
+struct TileStep {
+    int single = -1;
+    Echelon span;
+    std::vector<int> members;
+};
+std::vector<TileStep> group_tile_steps(const std::vector<CircOp> &ops, int N, int T, int precision, int rule,
+                                       int max_grads);
+// The step's phases, operators and matrices; grads: with the sums that an
+// adjoint sweep forms at its parametrised gadgets.
+void encode_step(Pass &p, const Echelon &E, const std::vector<const CircOp *> &recorded, bool mfma, bool grads);
+// A step of the adjoint sweep on psi and lam (tiles of 2^9 to 2^12
+// amplitudes): gradient g's partial sums go to gpart[g blocks ..].
+int launch_adjoint_pass(qs_qureg *psi, qs_qureg *lam, const Pass &p, const void *dev, double *gpart, unsigned blocks);
 size_t tile_pass_bytes(const Pass &p, int precision);
 void pack_tile_pass(const Pass &p, int precision, void *out);
 int launch_tile_pass(qs_qureg *q, const Pass &p, const void *dev);
@@ -116,6 +175,9 @@ void wait_circuit_uses(qs_circuit *c);
 
 Pass single_pass(const CircOp &op);
 
+// The steps of a circuit's adjoint sweep with their buffers (adjoint.hip).
+struct AdjointPlan;
+
 }  // namespace qs
 
 struct qs_circuit {
@@ -134,4 +196,8 @@ struct qs_circuit {
     // one event per stream the circuit's passes were queued on, recorded after
     // the last of them: tables and kernels are released only once they passed
     std::vector<std::pair<void *, void *>> uses;   // (hipStream_t, hipEvent_t)
+    // steps of the last adjoint sweep, kept for the next one: a sweep takes
+    // them out and puts them back (concurrent sweeps build their own)
+    std::mutex adjoint_mu;
+    std::shared_ptr<qs::AdjointPlan> adjoint;
 };

@@ -106,6 +106,11 @@ int stage_matrix(qs_qureg *q, const void *host, size_t bytes, const void **dev);
 
 // Device reduction helpers, defined in reduce.hip.
 int finish_reduction(qs_qureg *q, int blocks, int width, double *out);
+// Queue, without waiting: <a|b> of two statevectors on a's stream into
+// out[0..1] (device; a->d_partials as scratch); the fixed-order sums of `rows`
+// rows of `count` doubles into out[0..rows).
+int queue_inner_product(qs_qureg *a, const qs_qureg *b, double *out);
+int queue_row_sums(hipStream_t stream, const double *partials, int rows, int count, double *out);
 // Doubles of q->d_partials that the Pauli-sum expectation value uses at most.
 constexpr size_t kExpecPartials = 2 * (size_t)kReduceBlocks;
 // The Pauli-sum expectation value of qs_calc_expec_pauli_sum on q, whose

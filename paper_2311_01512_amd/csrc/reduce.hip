@@ -606,6 +606,30 @@ static int run_reduce(qs_qureg *q, const F &f, uint64_t n, int slot)
     return QS_OK;
 }
 
+int queue_inner_product(qs_qureg *a, const qs_qureg *b, double *out)
+{
+    const int blocks = (int)grid_for(a->num_amps, 256, kReduceBlocks);
+    if (a->precision == QS_C64) {
+        const Inner<float> f{(const float2 *)a->amps, (const float2 *)b->amps};
+        hipLaunchKernelGGL(k_reduce<Inner<float>>, dim3(blocks), dim3(256), 0, a->stream, f, a->num_amps, a->d_partials);
+    } else {
+        const Inner<double> f{(const double2 *)a->amps, (const double2 *)b->amps};
+        hipLaunchKernelGGL(k_reduce<Inner<double>>, dim3(blocks), dim3(256), 0, a->stream, f, a->num_amps, a->d_partials);
+    }
+    QS_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, a->stream, (const double *)a->d_partials, blocks, out, 0);
+    QS_LAUNCH_CHECK();
+    return QS_OK;
+}
+
+int queue_row_sums(hipStream_t stream, const double *partials, int rows, int count, double *out)
+{
+    if (rows < 1) return QS_OK;
+    hipLaunchKernelGGL(k_finalize_terms, dim3(rows), dim3(256), 0, stream, partials, count, out, 0);
+    QS_LAUNCH_CHECK();
+    return QS_OK;
+}
+
 // Copies result slots [0, nslots) back and waits.
 static int fetch(qs_qureg *q, int nslots)
 {

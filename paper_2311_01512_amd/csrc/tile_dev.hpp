@@ -277,74 +277,76 @@ __device__ __forceinline__ void mfma_dense(float2 (&x)[kRegs], const ROp &op, ui
     }
 }
 
-template <typename R>
-__device__ __forceinline__ void apply_reg_op(C2<R> (&x)[kRegs], const ROp &op, uint32_t tau, uint64_t base,
-                                             const C2<R> *__restrict__ mats)
+// Applies the operator to the register set(s) x...: one dispatch for all of
+// them (an adjoint sweep holds two states).
+template <typename R, typename... Xs>
+__device__ __forceinline__ void apply_reg_op(const ROp &op, uint32_t tau, uint64_t base,
+                                             const C2<R> *__restrict__ mats, Xs &...x)
 {
     constexpr bool f32 = same_type<R, float>::value;
     const C2<R> *m = mats + op.mat;
     // one switch (a jump table) over every operator code
     switch (op.code) {
-    case 1: reg_dense<R, 1, false>(x, op, tau, base, m); break;
-    case 2: reg_dense<R, 2, false>(x, op, tau, base, m); break;
-    case 3: reg_dense<R, 3, false>(x, op, tau, base, m); break;
-    case 4: reg_dense<R, 4, false>(x, op, tau, base, m); break;
-    case 5: reg_dense<R, 5, false>(x, op, tau, base, m); break;
-    case 6: reg_dense<R, 6, false>(x, op, tau, base, m); break;
-    case 7: reg_dense<R, 7, false>(x, op, tau, base, m); break;
-    case 8: reg_gadget<R, 0>(x, op, tau, base); break;
-    case 9: reg_gadget<R, 1>(x, op, tau, base); break;
-    case 10: reg_gadget<R, 2>(x, op, tau, base); break;
-    case 11: reg_gadget<R, 3>(x, op, tau, base); break;
-    case 12: reg_gadget<R, 4>(x, op, tau, base); break;
-    case 13: reg_gadget<R, 5>(x, op, tau, base); break;
-    case 14: reg_gadget<R, 6>(x, op, tau, base); break;
-    case 15: reg_gadget<R, 7>(x, op, tau, base); break;
-    case 16: reg_scale<R>(x, op); break;
-    case 24: reg_gadget_f<R, 0, true>(x, op, tau, base); break;
-    case 25: reg_gadget_f<R, 1, true>(x, op, tau, base); break;
-    case 26: reg_gadget_f<R, 2, true>(x, op, tau, base); break;
-    case 27: reg_gadget_f<R, 3, true>(x, op, tau, base); break;
-    case 28: reg_gadget_f<R, 4, true>(x, op, tau, base); break;
-    case 29: reg_gadget_f<R, 5, true>(x, op, tau, base); break;
-    case 30: reg_gadget_f<R, 6, true>(x, op, tau, base); break;
-    case 31: reg_gadget_f<R, 7, true>(x, op, tau, base); break;
-    case 41: reg_gadget_f<R, 1, false>(x, op, tau, base); break;
-    case 42: reg_gadget_f<R, 2, false>(x, op, tau, base); break;
-    case 43: reg_gadget_f<R, 3, false>(x, op, tau, base); break;
-    case 44: reg_gadget_f<R, 4, false>(x, op, tau, base); break;
-    case 45: reg_gadget_f<R, 5, false>(x, op, tau, base); break;
-    case 46: reg_gadget_f<R, 6, false>(x, op, tau, base); break;
-    case 47: reg_gadget_f<R, 7, false>(x, op, tau, base); break;
-    case 17: reg_dense<R, 1, true>(x, op, tau, base, m); break;
-    case 18: reg_dense<R, 2, true>(x, op, tau, base, m); break;
-    case 19: reg_dense<R, 3, true>(x, op, tau, base, m); break;
-    case 20: reg_dense<R, 4, true>(x, op, tau, base, m); break;
-    case 21: reg_dense<R, 5, true>(x, op, tau, base, m); break;
-    case 22: reg_dense<R, 6, true>(x, op, tau, base, m); break;
-    case 23: reg_dense<R, 7, true>(x, op, tau, base, m); break;
-    case 32: if constexpr (f32) mfma_dense<0>(x, op, tau, base, mats); break;
-    case 33: if constexpr (f32) mfma_dense<1>(x, op, tau, base, mats); break;
-    case 34: if constexpr (f32) mfma_dense<2>(x, op, tau, base, mats); break;
-    case 35: if constexpr (f32) mfma_dense<3>(x, op, tau, base, mats); break;
-    case 36: if constexpr (f32) mfma_dense<4>(x, op, tau, base, mats); break;
-    case 37: if constexpr (f32) mfma_dense<5>(x, op, tau, base, mats); break;
-    case 38: if constexpr (f32) mfma_dense<6>(x, op, tau, base, mats); break;
-    case 64 + 4 * 1: reg_sparse<R, 1, 0>(x, m); break;
-    case 64 + 4 * 2: reg_sparse<R, 2, 0>(x, m); break;
-    case 64 + 4 * 4: reg_sparse<R, 4, 0>(x, m); break;
-    case 64 + 4 * 3: reg_sparse<R, 3, 0>(x, m); break;
-    case 64 + 4 * 3 + 1: reg_sparse<R, 3, 1>(x, m); break;
-    case 64 + 4 * 3 + 2: reg_sparse<R, 3, 2>(x, m); break;
-    case 64 + 4 * 3 + 3: reg_sparse<R, 3, 3>(x, m); break;
-    case 64 + 4 * 5: reg_sparse<R, 5, 0>(x, m); break;
-    case 64 + 4 * 5 + 1: reg_sparse<R, 5, 1>(x, m); break;
-    case 64 + 4 * 5 + 2: reg_sparse<R, 5, 2>(x, m); break;
-    case 64 + 4 * 5 + 3: reg_sparse<R, 5, 3>(x, m); break;
-    case 64 + 4 * 6: reg_sparse<R, 6, 0>(x, m); break;
-    case 64 + 4 * 6 + 1: reg_sparse<R, 6, 1>(x, m); break;
-    case 64 + 4 * 6 + 2: reg_sparse<R, 6, 2>(x, m); break;
-    case 64 + 4 * 6 + 3: reg_sparse<R, 6, 3>(x, m); break;
+    case 1: (reg_dense<R, 1, false>(x, op, tau, base, m), ...); break;
+    case 2: (reg_dense<R, 2, false>(x, op, tau, base, m), ...); break;
+    case 3: (reg_dense<R, 3, false>(x, op, tau, base, m), ...); break;
+    case 4: (reg_dense<R, 4, false>(x, op, tau, base, m), ...); break;
+    case 5: (reg_dense<R, 5, false>(x, op, tau, base, m), ...); break;
+    case 6: (reg_dense<R, 6, false>(x, op, tau, base, m), ...); break;
+    case 7: (reg_dense<R, 7, false>(x, op, tau, base, m), ...); break;
+    case 8: (reg_gadget<R, 0>(x, op, tau, base), ...); break;
+    case 9: (reg_gadget<R, 1>(x, op, tau, base), ...); break;
+    case 10: (reg_gadget<R, 2>(x, op, tau, base), ...); break;
+    case 11: (reg_gadget<R, 3>(x, op, tau, base), ...); break;
+    case 12: (reg_gadget<R, 4>(x, op, tau, base), ...); break;
+    case 13: (reg_gadget<R, 5>(x, op, tau, base), ...); break;
+    case 14: (reg_gadget<R, 6>(x, op, tau, base), ...); break;
+    case 15: (reg_gadget<R, 7>(x, op, tau, base), ...); break;
+    case 16: (reg_scale<R>(x, op), ...); break;
+    case 24: (reg_gadget_f<R, 0, true>(x, op, tau, base), ...); break;
+    case 25: (reg_gadget_f<R, 1, true>(x, op, tau, base), ...); break;
+    case 26: (reg_gadget_f<R, 2, true>(x, op, tau, base), ...); break;
+    case 27: (reg_gadget_f<R, 3, true>(x, op, tau, base), ...); break;
+    case 28: (reg_gadget_f<R, 4, true>(x, op, tau, base), ...); break;
+    case 29: (reg_gadget_f<R, 5, true>(x, op, tau, base), ...); break;
+    case 30: (reg_gadget_f<R, 6, true>(x, op, tau, base), ...); break;
+    case 31: (reg_gadget_f<R, 7, true>(x, op, tau, base), ...); break;
+    case 41: (reg_gadget_f<R, 1, false>(x, op, tau, base), ...); break;
+    case 42: (reg_gadget_f<R, 2, false>(x, op, tau, base), ...); break;
+    case 43: (reg_gadget_f<R, 3, false>(x, op, tau, base), ...); break;
+    case 44: (reg_gadget_f<R, 4, false>(x, op, tau, base), ...); break;
+    case 45: (reg_gadget_f<R, 5, false>(x, op, tau, base), ...); break;
+    case 46: (reg_gadget_f<R, 6, false>(x, op, tau, base), ...); break;
+    case 47: (reg_gadget_f<R, 7, false>(x, op, tau, base), ...); break;
+    case 17: (reg_dense<R, 1, true>(x, op, tau, base, m), ...); break;
+    case 18: (reg_dense<R, 2, true>(x, op, tau, base, m), ...); break;
+    case 19: (reg_dense<R, 3, true>(x, op, tau, base, m), ...); break;
+    case 20: (reg_dense<R, 4, true>(x, op, tau, base, m), ...); break;
+    case 21: (reg_dense<R, 5, true>(x, op, tau, base, m), ...); break;
+    case 22: (reg_dense<R, 6, true>(x, op, tau, base, m), ...); break;
+    case 23: (reg_dense<R, 7, true>(x, op, tau, base, m), ...); break;
+    case 32: if constexpr (f32) (mfma_dense<0>(x, op, tau, base, mats), ...); break;
+    case 33: if constexpr (f32) (mfma_dense<1>(x, op, tau, base, mats), ...); break;
+    case 34: if constexpr (f32) (mfma_dense<2>(x, op, tau, base, mats), ...); break;
+    case 35: if constexpr (f32) (mfma_dense<3>(x, op, tau, base, mats), ...); break;
+    case 36: if constexpr (f32) (mfma_dense<4>(x, op, tau, base, mats), ...); break;
+    case 37: if constexpr (f32) (mfma_dense<5>(x, op, tau, base, mats), ...); break;
+    case 38: if constexpr (f32) (mfma_dense<6>(x, op, tau, base, mats), ...); break;
+    case 64 + 4 * 1: (reg_sparse<R, 1, 0>(x, m), ...); break;
+    case 64 + 4 * 2: (reg_sparse<R, 2, 0>(x, m), ...); break;
+    case 64 + 4 * 4: (reg_sparse<R, 4, 0>(x, m), ...); break;
+    case 64 + 4 * 3: (reg_sparse<R, 3, 0>(x, m), ...); break;
+    case 64 + 4 * 3 + 1: (reg_sparse<R, 3, 1>(x, m), ...); break;
+    case 64 + 4 * 3 + 2: (reg_sparse<R, 3, 2>(x, m), ...); break;
+    case 64 + 4 * 3 + 3: (reg_sparse<R, 3, 3>(x, m), ...); break;
+    case 64 + 4 * 5: (reg_sparse<R, 5, 0>(x, m), ...); break;
+    case 64 + 4 * 5 + 1: (reg_sparse<R, 5, 1>(x, m), ...); break;
+    case 64 + 4 * 5 + 2: (reg_sparse<R, 5, 2>(x, m), ...); break;
+    case 64 + 4 * 5 + 3: (reg_sparse<R, 5, 3>(x, m), ...); break;
+    case 64 + 4 * 6: (reg_sparse<R, 6, 0>(x, m), ...); break;
+    case 64 + 4 * 6 + 1: (reg_sparse<R, 6, 1>(x, m), ...); break;
+    case 64 + 4 * 6 + 2: (reg_sparse<R, 6, 2>(x, m), ...); break;
+    case 64 + 4 * 6 + 3: (reg_sparse<R, 6, 3>(x, m), ...); break;
     default: break;
     }
 }

@@ -32,37 +32,6 @@
 
 namespace qs {
 
-// ---- GF(2) reduced echelon basis ----------------------------------------------------
-
-struct Echelon {
-    std::map<int, uint64_t> by_pivot;   // pivot bit -> vector (pivot = highest set bit)
-
-    uint64_t reduce(uint64_t x) const
-    {
-        for (auto it = by_pivot.rbegin(); it != by_pivot.rend(); ++it)
-            if ((x >> it->first) & 1ULL) x ^= it->second;
-        return x;
-    }
-    // Adds x; keeps every pivot bit set in exactly one vector.
-    bool add(uint64_t x)
-    {
-        x = reduce(x);
-        if (!x) return false;
-        const int p = 63 - __builtin_clzll(x);
-        for (auto &kv : by_pivot)
-            if ((kv.second >> p) & 1ULL) kv.second ^= x;
-        by_pivot[p] = x;
-        return true;
-    }
-    int dim() const { return (int)by_pivot.size(); }
-    int dim_with(const std::vector<uint64_t> &xs) const
-    {
-        Echelon e = *this;
-        for (uint64_t x : xs) e.add(x);
-        return e.dim();
-    }
-};
-
 // Gates of up to 3 targets run on registers; 4-target gates only on the
 // matrix cores (complex64 tiles of at least 2^9 amplitudes).
 static bool absorbable(const CircOp &op, bool mfma)
@@ -296,7 +265,7 @@ static std::vector<const CircOp *> fuse_members(const std::vector<const CircOp *
     return out;
 }
 
-static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircOp *> &recorded, bool mfma)
+void encode_step(Pass &p, const Echelon &E, const std::vector<const CircOp *> &recorded, bool mfma, bool grads)
 {
     std::deque<CircOp> fused;
     const std::vector<const CircOp *> members = fuse_members(recorded, fused);
@@ -410,6 +379,7 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
     p.phases.clear();
     p.rops.clear();
     p.tmats.clear();
+    p.grads.clear();
     // Gadgets run as cos(theta) (1 + i tan(theta) eta P): the real factors
     // cos(theta) of the step multiply every amplitude alike, so they are
     // collected in `scale` and folded into one uncontrolled matrix of the step
@@ -418,6 +388,8 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
     // keep the unfactored form, as do all once the step's growth bound would
     // pass 2^64.
     double scale = 1.0, growth = 1.0;
+    std::vector<double> taken_out;   // each operator's factor moved into scale
+    size_t fold_at = ~size_t(0);     // operator whose matrix took scale
     std::vector<std::pair<size_t, size_t>> mat_range;   // tmats entries of each operator
     // A phase takes, in order, every remaining member that fits it and
     // commutes with each remaining member it jumps over.
@@ -495,6 +467,7 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
             const Need &n = needs[m];
             const size_t mat0 = p.tmats.size();
             ROp ro{};
+            taken_out.push_back(1.0);
             if (op->gadget) {
                 uint32_t f = n.flip, fu = 0;
                 while (f) {
@@ -527,6 +500,7 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
                     ro.pre = partner * k;
                     ro.pim = 0.0;
                     scale *= cs;
+                    taken_out.back() = cs;
                     growth *= 1.0 + tn;
                 } else {
                     ro.code = 8 + (int)fu;
@@ -541,6 +515,14 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
                 ro.fcim = (float)ro.cim;
                 ro.fpre = (float)ro.pre;
                 ro.fpim = (float)ro.pim;
+                if (grads && op->param >= 0) {
+                    // adjoint sweep: dE/dparam -= 2 scale Im(i^{#Y} w), w the
+                    // sum that the kernel forms (its Im for an even #Y, its Re
+                    // for an odd one, ro.mat)
+                    p.grads.push_back({op->param, (n.ny & 2 ? 2.0 : -2.0) * op->scale, p.rops.size()});
+                    ro.nc = (int)p.grads.size();
+                    ro.mat = n.ny & 1;
+                }
             } else {
                 ro.nc = (int)op->ctrls.size();
                 for (int q = 0; q < ro.nc; q++) {
@@ -612,6 +594,7 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
                 if ((pass == 0 ? reg : core) && mat_range[i].second > mat_range[i].first) {
                     for (size_t k = mat_range[i].first; k < mat_range[i].second; k++) p.tmats[k] *= scale;
                     folded = true;
+                    fold_at = i;
                 }
             }
         if (!folded) {
@@ -623,41 +606,64 @@ static void encode_step(Pass &p, const Echelon &E, const std::vector<const CircO
             p.phases.back().num_ops++;
         }
     }
+    // At a gradient the registers hold both states times the same real factor
+    // 1 / f: the factors taken out so far, less `scale` once a matrix took it.
+    double f = 1.0;
+    size_t g = 0;
+    for (size_t i = 0; i < taken_out.size(); i++) {
+        if (g < p.grads.size() && p.grads[g].rop == i) p.grads[g++].weight *= f * f;
+        f *= taken_out[i];
+        if (i == fold_at) f /= scale;
+    }
     p.members = (int)recorded.size();
 }
 
-void plan_tiles(qs_circuit *c, int T, int precision)
+// Groups operators into tile steps of at most T dimensions under one
+// admission rule.  Rule g < 0: one greedy sweep over the window.  Rule
+// g >= 0: a first sweep admits only operators that grow the span by at most g
+// dimensions (the step's first operator always), then the greedy sweep.
+// Either way an operator joins a step only if it commutes with every earlier
+// operator left out, so it also commutes with every member placed after it in
+// circuit order: the member list is a valid order of application.  A step
+// takes at most max_grads parametrised gadgets.
+std::vector<TileStep> group_tile_steps(const std::vector<CircOp> &ops, int N, int T, int precision, int rule,
+                                       int max_grads)
 {
-    const int N = c->index_bits;
-    const int n_ops = (int)c->ops.size();
+    const int n_ops = (int)ops.size();
     const int C = std::min(N, tile_low_qubits(precision));
-    T = std::min(T, N);
     // dense gates of 2-4 targets on the FP32 matrix cores (complex64 only)
     const bool mfma = precision == QS_C64 && T >= kRegBits + 6;
     const int lookahead = 512;
     std::vector<OpMasks> masks(n_ops);
     std::vector<std::vector<uint64_t>> needs(n_ops);
     for (int i = 0; i < n_ops; i++) {
-        masks[i] = op_masks(c->ops[i]);
-        needs[i] = needed_vectors(c->ops[i]);
+        masks[i] = op_masks(ops[i]);
+        needs[i] = needed_vectors(ops[i]);
     }
-    // Admission rules for one step.  Rule g < 0: one greedy sweep over the
-    // window.  Rule g >= 0: a first sweep admits only operators that grow the
-    // span by at most g dimensions (the step's first operator always), then
-    // the greedy sweep.  Either way an operator joins a step only if it
-    // commutes with every earlier operator left out, so it also commutes
-    // with every member placed after it in circuit order: the member list
-    // is a valid order of application.
-    auto build_step = [&](int i, int g, std::vector<char> &placed, Echelon &E,
-                          std::vector<const CircOp *> &members) {
+    std::vector<TileStep> out;
+    std::vector<char> placed(n_ops, 0);
+    for (int i = 0; i < n_ops; i++) {
+        if (placed[i]) continue;
+        TileStep st;
+        // registers need a tile of more than kRegBits dimensions; controls
+        // beyond the 4 a tile operator carries, or gates of more than 3
+        // targets, run as passes of their own
+        if (T <= kRegBits || !absorbable(ops[i], mfma) || ops[i].ctrls.size() > 4) {
+            placed[i] = 1;
+            st.single = i;
+            out.push_back(std::move(st));
+            continue;
+        }
+        Echelon &E = st.span;
+        int grads = 0;
         for (int b = 0; b < C; b++) E.add(1ULL << b);
-        for (int sweep = g < 0 ? 1 : 0; sweep < 2; sweep++) {
+        for (int sweep = rule < 0 ? 1 : 0; sweep < 2; sweep++) {
             // operators the step leaves out: a later operator joins only if
             // it commutes with every one of them
             std::vector<int> skipped;
             for (int j = i; j < n_ops && j < i + lookahead; j++) {
                 if (placed[j]) continue;
-                const CircOp &op = c->ops[j];
+                const CircOp &op = ops[j];
                 bool free = true;
                 for (int k : skipped)
                     if (!ops_commute(masks[j], masks[k])) {
@@ -668,53 +674,50 @@ void plan_tiles(qs_circuit *c, int T, int precision)
                     skipped.push_back(j);
                     continue;
                 }
+                const bool grad = op.gadget && op.param >= 0;
                 const int dim = E.dim_with(needs[j]);
                 const bool fits = absorbable(op, mfma) && op.ctrls.size() <= 4 && dim <= T &&
-                                  (sweep == 1 || j == i || dim - E.dim() <= g);
+                                  (sweep == 1 || j == i || dim - E.dim() <= rule) && (!grad || grads < max_grads);
                 if (fits) {
                     for (uint64_t x : needs[j]) E.add(x);
-                    members.push_back(&op);
+                    st.members.push_back(j);
                     placed[j] = 1;
+                    grads += grad;
                 } else {
                     skipped.push_back(j);
                 }
             }
         }
-    };
-    // one plan per rule, the same rule for every step
-    auto plan = [&](int rule, std::vector<Pass> &out) {
-        std::vector<char> placed(n_ops, 0);
-        for (int i = 0; i < n_ops; i++) {
-            if (placed[i]) continue;
-            const CircOp &first = c->ops[i];
-            // registers need a tile of more than kRegBits dimensions; controls
-            // beyond the 4 a tile operator carries, or gates of more than 3
-            // targets, run as passes of their own
-            if (T <= kRegBits || !absorbable(first, mfma) || first.ctrls.size() > 4) {
-                placed[i] = 1;
-                out.push_back(single_pass(first));
-                continue;
-            }
-            Echelon E;
-            std::vector<const CircOp *> members;
-            build_step(i, rule, placed, E, members);
-            // fill the tile to T dimensions with the lowest free qubits: longer
-            // contiguous runs, fewer and larger tiles
-            for (int b = C; b < N && E.dim() < T; b++) E.add(1ULL << b);
-            Pass p{};
-            encode_step(p, E, members, mfma);
-            out.push_back(std::move(p));
-        }
-    };
-    // the plan with the fewest passes wins (ties to the plain greedy)
-    std::vector<Pass> best;
-    plan(-1, best);
-    for (int rule : {0, 1}) {
-        std::vector<Pass> alt;
-        plan(rule, alt);
-        if (alt.size() < best.size()) best.swap(alt);
+        // fill the tile to T dimensions with the lowest free qubits: longer
+        // contiguous runs, fewer and larger tiles
+        for (int b = C; b < N && E.dim() < T; b++) E.add(1ULL << b);
+        out.push_back(std::move(st));
     }
-    for (Pass &p : best) c->passes.push_back(std::move(p));
+    return out;
+}
+
+void plan_tiles(qs_circuit *c, int T, int precision)
+{
+    const int N = c->index_bits;
+    T = std::min(T, N);
+    // one plan per rule, the same rule for every step; the plan with the
+    // fewest passes wins (ties to the plain greedy)
+    std::vector<TileStep> best;
+    for (int rule : {-1, 0, 1}) {
+        std::vector<TileStep> alt = group_tile_steps(c->ops, N, T, precision, rule, 1 << 30);
+        if (rule < 0 || alt.size() < best.size()) best.swap(alt);
+    }
+    for (const TileStep &st : best) {
+        if (st.single >= 0) {
+            c->passes.push_back(single_pass(c->ops[st.single]));
+            continue;
+        }
+        std::vector<const CircOp *> members;
+        for (int j : st.members) members.push_back(&c->ops[j]);
+        Pass p{};
+        encode_step(p, st.span, members, precision == QS_C64 && T >= kRegBits + 6, false);
+        c->passes.push_back(std::move(p));
+    }
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -770,9 +773,152 @@ __global__ __launch_bounds__(1024) void k_tile_step(C2<R> *__restrict__ a, TileA
             const RPhase &P = ph[p];
             if (p > 0) tau = tile_exchange<R>(x, lds_raw, tau, ph[p - 1], P);
             const int end = P.first_op + P.num_ops;
-            for (int o = P.first_op; o < end; o++) apply_reg_op<R>(x, ops[o], tau, base, mats);
+            for (int o = P.first_op; o < end; o++) apply_reg_op<R>(ops[o], tau, base, mats, x);
         }
     });
+}
+
+// One real sum per parametrised gadget, before the sweep applies its adjoint:
+// over the thread's registers, the Im (Re for an odd number of Y: RE) of
+// conj(lambda_i) psi_j (-1)^{popc(j & yz)}, j = i ^ x.  The signs of j and of
+// its partner differ by (-1)^{#Y}.
+template <typename R, int FU>
+__device__ __forceinline__ double reg_grad(const C2<R> (&x)[kRegs], const C2<R> (&y)[kRegs], const ROp &op,
+                                           uint32_t tau, uint64_t base)
+{
+    const uint32_t st = (uint32_t)(__popcll(base & op.yz) + __popc(tau & op.yzm)) & 1u;
+    const bool re = op.mat != 0;
+    auto part = [&](const C2<R> &l, const C2<R> &p) {   // of conj(l) p
+        return re ? fma((double)l.x, (double)p.x, (double)l.y * (double)p.y)
+                  : fma((double)l.x, (double)p.y, -((double)l.y * (double)p.x));
+    };
+    constexpr int HB = FU ? 31 - __builtin_clz((unsigned)FU) : 0;
+    double sum = 0.0;
+#pragma unroll
+    for (int u0 = 0; u0 < kRegs; u0++) {
+        double v;
+        if constexpr (FU == 0) {
+            v = part(y[u0], x[u0]);
+        } else {
+            if ((u0 >> HB) & 1) continue;
+            const double a = part(y[u0], x[u0 ^ FU]), b = part(y[u0 ^ FU], x[u0]);
+            v = re ? b - a : b + a;
+        }
+        sum += (__popc((uint32_t)u0 & op.gy) & 1) ? -v : v;
+    }
+    return st ? -sum : sum;
+}
+
+// A step of the adjoint sweep: psi (a) and lambda (l) through the same tile
+// step, whose operators are the adjoints of a circuit step's, last first, and
+// the sums of the step's parametrised gadgets.  One read and one write of
+// both states for all of them.  Both tiles take turns in one LDS buffer, so
+// that complex128 tiles of 2^11 leave room for four blocks per CU.  A block
+// keeps a sum per gadget and wavefront over all its tiles (red, after the
+// tile).  Bound: the serial chain of a tile (operator records and matrices
+// from memory, exchanges), with 12 waves per CU in flight: 78 us per step on
+// 22 qubits in complex128 (256 MiB moved, 3.4 TB/s).  Energy and 30 gradients
+// of 45 operators there: 4.43 ms with one operator per pass, 1.00 ms so.
+template <typename R>
+__global__ __launch_bounds__(512) void k_tile_adjoint(C2<R> *__restrict__ a, C2<R> *__restrict__ l, TileArgs ta,
+                                                       int num_grads, const RPhase *__restrict__ ph,
+                                                       const ROp *__restrict__ ops, const C2<R> *__restrict__ mats,
+                                                       double *__restrict__ gpart)
+{
+    extern __shared__ unsigned char lds_raw[];
+    double *red = reinterpret_cast<double *>(lds_raw + (sizeof(C2<R>) << ta.d));
+    const uint32_t t = threadIdx.x;
+    const int lane = (int)(t & 63u), wave = (int)(t >> 6), nw = (int)(blockDim.x >> 6);
+    for (int i = (int)t; i < num_grads * nw; i += (int)blockDim.x) red[i] = 0.0;
+    __syncthreads();
+    const int lb = ta.d - kRegBits;
+    const RPhase &first = ph[0], &last = ph[ta.nph - 1];
+    const uint64_t xg = thread_offset(t, lb, first), xs = thread_offset(t, lb, last);
+    for (uint64_t tile = blockIdx.x; tile < ta.num_tiles; tile += gridDim.x) {
+        const uint64_t base = insert_zeros(tile, ta.plan);
+        C2<R> x[kRegs], y[kRegs];
+#pragma unroll
+        for (int u = 0; u < kRegs; u++) {
+            const uint64_t i = base ^ xg ^ first.yaddr[u];
+            x[u] = a[i];
+            y[u] = l[i];
+        }
+        uint32_t tau = tau_of(t, first);
+        for (int p = 0; p < ta.nph; p++) {
+            const RPhase &P = ph[p];
+            if (p > 0) {
+                const uint32_t from = tau;
+                tau = tile_exchange<R>(x, lds_raw, from, ph[p - 1], P);
+                tile_exchange<R>(y, lds_raw, from, ph[p - 1], P);
+            }
+            const int end = P.first_op + P.num_ops;
+            for (int o = P.first_op; o < end; o++) {
+                const ROp &op = ops[o];
+                // gadget codes: 8-15, 24-31, 40-47; nc numbers the gradients
+                if (op.code < 48 && (op.code & 8) && op.nc > 0) {
+                    double v = 0.0;
+                    switch (op.code & 7) {
+                    case 0: v = reg_grad<R, 0>(x, y, op, tau, base); break;
+                    case 1: v = reg_grad<R, 1>(x, y, op, tau, base); break;
+                    case 2: v = reg_grad<R, 2>(x, y, op, tau, base); break;
+                    case 3: v = reg_grad<R, 3>(x, y, op, tau, base); break;
+                    case 4: v = reg_grad<R, 4>(x, y, op, tau, base); break;
+                    case 5: v = reg_grad<R, 5>(x, y, op, tau, base); break;
+                    case 6: v = reg_grad<R, 6>(x, y, op, tau, base); break;
+                    default: v = reg_grad<R, 7>(x, y, op, tau, base); break;
+                    }
+#pragma unroll
+                    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+                    if (lane == 0) red[(op.nc - 1) * nw + wave] += v;
+                }
+                apply_reg_op<R>(op, tau, base, mats, x, y);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kRegs; u++) {
+            const uint64_t i = base ^ xs ^ last.yaddr[u];
+            a[i] = x[u];
+            l[i] = y[u];
+        }
+    }
+    __syncthreads();
+    for (int g = (int)t; g < num_grads; g += (int)blockDim.x) {
+        double v = 0.0;
+        for (int w = 0; w < nw; w++) v += red[g * nw + w];
+        gpart[(size_t)g * gridDim.x + blockIdx.x] = v;
+    }
+}
+
+static TileArgs tile_args(const qs_qureg *q, const Pass &p)
+{
+    TileArgs ta{};
+    ta.d = p.tile_d;
+    ta.nph = (int)p.phases.size();
+    ta.plan = make_insert_plan(p.pivots);
+    ta.num_tiles = 1ULL << (q->index_bits - p.tile_d);
+    return ta;
+}
+
+int launch_adjoint_pass(qs_qureg *psi, qs_qureg *lam, const Pass &p, const void *dev, double *gpart, unsigned blocks)
+{
+    if (p.phases.empty()) return QS_OK;
+    if (p.tile_d < kRegBits + 6 || p.tile_d > kRegBits + 9) return fail(QS_E_ARG, "tile dimension out of range");
+    const TileArgs ta = tile_args(psi, p);
+    const unsigned char *d = (const unsigned char *)dev;
+    const ROp *ops = (const ROp *)(d + align256(p.phases.size() * sizeof(RPhase)));
+    const unsigned char *mats = (const unsigned char *)ops + align256(p.rops.size() * sizeof(ROp));
+    const unsigned block = 1u << (p.tile_d - kRegBits);
+    const int ng = (int)p.grads.size();
+    const size_t ab = psi->precision == QS_C64 ? sizeof(float2) : sizeof(double2);
+    const size_t lds = (ab << p.tile_d) + sizeof(double) * ng * (block / 64);
+    if (psi->precision == QS_C64)
+        hipLaunchKernelGGL(k_tile_adjoint<float>, dim3(blocks), dim3(block), lds, psi->stream, (float2 *)psi->amps,
+                           (float2 *)lam->amps, ta, ng, (const RPhase *)d, ops, (const float2 *)mats, gpart);
+    else
+        hipLaunchKernelGGL(k_tile_adjoint<double>, dim3(blocks), dim3(block), lds, psi->stream, (double2 *)psi->amps,
+                           (double2 *)lam->amps, ta, ng, (const RPhase *)d, ops, (const double2 *)mats, gpart);
+    QS_LAUNCH_CHECK();
+    return QS_OK;
 }
 
 int launch_tile_pass(qs_qureg *q, const Pass &p, const void *dev)
@@ -780,11 +926,7 @@ int launch_tile_pass(qs_qureg *q, const Pass &p, const void *dev)
     if (!dev) return fail(QS_E_PRECOND, "tile pass without device tables");
     if (p.phases.empty()) return QS_OK;
     if (p.tile_d <= kRegBits || p.tile_d > kTileDimMax) return fail(QS_E_ARG, "tile dimension out of range");
-    TileArgs ta{};
-    ta.d = p.tile_d;
-    ta.nph = (int)p.phases.size();
-    ta.plan = make_insert_plan(p.pivots);
-    ta.num_tiles = 1ULL << (q->index_bits - p.tile_d);
+    TileArgs ta = tile_args(q, p);
     const unsigned char *d = (const unsigned char *)dev;
     const RPhase *ph = (const RPhase *)d;
     const ROp *ops = (const ROp *)(d + align256(p.phases.size() * sizeof(RPhase)));
