@@ -11,6 +11,7 @@
 // the circuit is respected.  All circuits' s-th steps form one kernel launch.
 #include "batch_dev.hpp"
 #include "circuit.hpp"
+#include "pauli_sum_dev.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -44,34 +45,6 @@ struct BCirc {
     int param_off;
 };
 
-struct DTerm {
-    uint64_t x, yz;
-    double cre, cim;  // h_n i^{#Y}
-};
-
-// (re, im) summed over the block; valid in thread 0.
-__device__ void bblock_sum2(double &re, double &im, double *scratch)
-{
-    re = bwave_sum(re);
-    im = bwave_sum(im);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) {
-        scratch[2 * wave] = re;
-        scratch[2 * wave + 1] = im;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double a = 0, b = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); w++) {
-            a += scratch[2 * w];
-            b += scratch[2 * w + 1];
-        }
-        re = a;
-        im = b;
-    }
-}
-
 __device__ __forceinline__ uint64_t tile_offset(int j, const DStep &st)
 {
     uint64_t o = 0;
@@ -79,17 +52,69 @@ __device__ __forceinline__ uint64_t tile_offset(int j, const DStep &st)
     return o;
 }
 
-// cos and sin of every rotation's angle scale * parameter, once per run.
-__global__ __launch_bounds__(256) void k_batch_trig(const DOp *__restrict__ ops, int num_ops,
-                                                     const double *__restrict__ params, double *__restrict__ trig)
+// A run of operators whose rotations' factors are applied together: some
+// phases of a register-path step, or (reg = 0, no factors) a step without.
+struct DSeg {
+    int op_begin, op_end;
+    int reg;
+};
+
+// The table entries of every rotation, once per run (one wavefront per
+// segment): cos and sin of its angle scale * parameter, or m and the form on
+// the register path, where the segment's factor in both directions is the
+// product of its rotations' factors, and a rotation's gradient gets the
+// square of those that the backward direction has left out when it comes to
+// it (both states lack them): the later ones of its segment.
+template <typename R>
+__global__ __launch_bounds__(256) void k_batch_trig(const DSeg *__restrict__ segs, int num_segs,
+                                                     const DOp *__restrict__ ops, const double *__restrict__ params,
+                                                     double *__restrict__ trig, double *__restrict__ scales,
+                                                     double *__restrict__ gscale)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= num_ops) return;
-    const DOp op = ops[k];
-    double s = 0.0, c = 1.0;
-    if (op.kind == BOP_ROT) sincos(op.scale * params[op.param], &s, &c);
-    trig[2 * k] = c;
-    trig[2 * k + 1] = s;
+    const int g = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+    if (g >= num_segs) return;
+    const DSeg sg = segs[g];
+    double after = 1.0, sign = 1.0;   // product of the factors of the operators handled so far (the later ones)
+    for (int end = sg.op_end; end > sg.op_begin; end -= 64) {
+        const int k = end - 64 + lane;
+        double f = 1.0, flip = 1.0;
+        int slot = -1;
+        if (k >= sg.op_begin) {
+            const DOp &op = ops[k];
+            if (op.kind == BOP_ROT) {
+                double s, c;
+                sincos(op.scale * params[op.param], &s, &c);
+                slot = op.grad;
+                if (sg.reg) {
+                    const bool form = fabs(c) >= fabs(s);
+                    f = form ? c : s;
+                    flip = form ? 1.0 : -1.0;
+                    *reinterpret_cast<RotM<R> *>(trig + 2 * k) = {(R)(form ? s / c : c / s), form ? 1u : 0u};
+                } else {
+                    trig[2 * k] = c;
+                    trig[2 * k + 1] = s;
+                }
+            }
+        }
+        // inclusive suffix products over the lanes
+        double p = f;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double q = __shfl_down(p, o, 64), r = __shfl_xor(flip, o, 64);
+            if (lane + o < 64) p *= q;
+            flip *= r;
+        }
+        double later = __shfl_down(p, 1, 64);
+        if (lane == 63) later = 1.0;
+        later *= after;
+        if (slot >= 0) gscale[slot] = later * later;
+        after *= __shfl(p, 0, 64);
+        sign *= flip;
+    }
+    if (sg.reg && lane == 0) {
+        scales[2 * g] = after;
+        scales[2 * g + 1] = sign * after;
+    }
 }
 
 template <typename R>
@@ -264,7 +289,8 @@ template <typename R>
 __global__ __launch_bounds__(512) void k_batch_forward_reg(C2<R> *__restrict__ amps, const DStep *__restrict__ steps,
                                                             const BPhase *__restrict__ phases,
                                                             const DOp *__restrict__ ops, const uint2 *__restrict__ work,
-                                                            const double *__restrict__ trig)
+                                                            const double *__restrict__ trig,
+                                                            const double *__restrict__ scales)
 {
     extern __shared__ unsigned char lds_raw[];
     C2<R> *v = reinterpret_cast<C2<R> *>(lds_raw);
@@ -288,7 +314,8 @@ __global__ __launch_bounds__(512) void k_batch_forward_reg(C2<R> *__restrict__ a
         if (p > st.ph_begin) tau = bphase_exchange<R>(x, v, tau, phases[p - 1], P, active);
         if (!active) continue;
         uint32_t czm = 0;   // sign mask of the current run of CZs
-        for (int k = P.op_begin; k < P.op_end; k++) fwd_op<R>(x, ops[k], k, trig, tau, base, czm);
+        for (int k = P.op_begin; k < P.op_end; k++) fwd_op<R>(x, ops[k], load_rot<R>(trig, k), tau, base, czm);
+        if (P.fscale >= 0) reg_scale8<R>(x, scales[2 * (st.seg_begin + P.fscale)]);
     }
     if (active) {
         const uint64_t xo = base | tile_offset_bits(tau, st);
@@ -302,9 +329,9 @@ __global__ __launch_bounds__(512) void k_batch_forward_reg(C2<R> *__restrict__ a
 // partial Im <lambda|P|phi> comes from the register pairs it couples, before
 // U^dagger is applied to both states.  Each row of 16 lanes leaves its
 // partial in the rotation's LDS slots; after the barrier that opens the next
-// exchange one thread per rotation adds the rows' partials (fixed order),
-// and those reads complete before the exchange's second barrier, after
-// which the next phase writes the slots again.
+// exchange 32 lanes per rotation add the rows' partials (fixed order), and
+// those reads complete before the exchange's second barrier, after which the
+// next phase writes the slots again.
 template <typename R>
 __global__ __launch_bounds__(512) void k_batch_backward_reg(C2<R> *__restrict__ amps, uint64_t lambda_base,
                                                              const DStep *__restrict__ steps,
@@ -312,6 +339,7 @@ __global__ __launch_bounds__(512) void k_batch_backward_reg(C2<R> *__restrict__ 
                                                              const DOp *__restrict__ ops,
                                                              const uint2 *__restrict__ work,
                                                              const double *__restrict__ trig,
+                                                             const double *__restrict__ scales,
                                                              double *__restrict__ gpart)
 {
     extern __shared__ unsigned char lds_raw[];
@@ -346,15 +374,21 @@ __global__ __launch_bounds__(512) void k_batch_backward_reg(C2<R> *__restrict__ 
         if (p < st.ph_end - 1) {
             const BPhase &D = phases[p + 1];   // the finished phase
             __syncthreads();   // earlier LDS reads done; the finished phase's partials visible
-            flush_phase(ops, D.op_begin, D.op_end, red, nwaves, w.y, gpart);
+            flush_phase(D, st, red, nwaves, w.y, gpart);
             tau = bphase_exchange2<R>(x, y, vphi, vlam, tau, D, P, active);
         }
         if (!active) continue;
         uint32_t czm = 0;   // sign mask of the current run of CZs
-        for (int k = P.op_end - 1; k >= P.op_begin; k--) bwd_op<R>(x, y, ops[k], k, trig, tau, base, czm, red, lane, wave);
+        for (int k = P.op_end - 1; k >= P.op_begin; k--)
+            bwd_op<R>(x, y, ops[k], load_rot<R>(trig, k), tau, base, czm, red, lane, wave);
+        if (P.bscale >= 0) {
+            const double f = scales[2 * (st.seg_begin + P.bscale) + 1];
+            reg_scale8<R>(x, f);
+            reg_scale8<R>(y, f);
+        }
     }
     __syncthreads();
-    flush_phase(ops, phases[st.ph_begin].op_begin, phases[st.ph_begin].op_end, red, nwaves, w.y, gpart);
+    flush_phase(phases[st.ph_begin], st, red, nwaves, w.y, gpart);
     if (active) {
         const uint64_t xo = base | tile_offset_bits(tau, st);
         const RegOffsets ro(phases[st.ph_begin], st);
@@ -367,100 +401,100 @@ __global__ __launch_bounds__(512) void k_batch_backward_reg(C2<R> *__restrict__ 
     }
 }
 
-// Per-block circuit table of the flat amplitude range.
-struct BlockMap {
-    const int *circ;         // circuit of each 256-amplitude block
-    const uint64_t *start;   // first local index of each block
-};
-
-// |0..0> in the listed 256-amplitude blocks.
+// |0..0> in the listed blocks of 256 amplitudes (circuit, block number in it).
 template <typename R>
-__global__ __launch_bounds__(256) void k_batch_init(C2<R> *__restrict__ amps, BlockMap bm, const int *__restrict__ blocks,
+__global__ __launch_bounds__(256) void k_batch_init(C2<R> *__restrict__ amps, const int2 *__restrict__ blocks,
                                                      const uint64_t *__restrict__ offs, const int *__restrict__ nq)
 {
-    const int blk = blocks[blockIdx.x];
-    const int c = bm.circ[blk];
-    const uint64_t i = bm.start[blk] + threadIdx.x;
+    const int c = blocks[blockIdx.x].x;
+    const uint64_t i = 256ULL * (uint64_t)blocks[blockIdx.x].y + threadIdx.x;
     if (i < (1ULL << nq[c])) amps[offs[c] + i] = mk<R>(i == 0 ? R(1) : R(0), R(0));
 }
 
-constexpr int kTermGroup = 4;   // Hamiltonian terms gathered together
+// A block of k_batch_hamiltonian: 256 U amplitudes of a circuit from index
+// `start` on (U = 4; 1 in circuits below 10 qubits, where threads beyond the
+// state idle), its energy partial's place.
+struct HBlock {
+    int circ, part;
+    uint64_t start;
+};
 
-// lambda = H phi with (P phi)_i = beta_{i^x} phi_{i^x}, beta_y = i^{#Y} (-1)^{popc(y & yz)};
-// energy partial sum_i conj(phi_i) lambda_i per block.
+// lambda = H phi (add_pauli_terms) and the block's partial of the energy
+// sum_i Re conj(phi_i) lambda_i.  term_off: each circuit's terms with real
+// coefficients, then those with imaginary ones.
+template <typename R, int U>
+__device__ __forceinline__ double hamiltonian_block(C2<R> *__restrict__ amps, uint64_t lambda_base, uint64_t off,
+                                                    uint64_t start, const PauliTerm *__restrict__ terms, int t0, int t1,
+                                                    int t2)
+{
+    const C2<R> *phi = amps + off;
+    const uint32_t t = threadIdx.x;
+    double re[U], im[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) re[u] = im[u] = 0.0;
+    add_pauli_terms<R, U, false>(re, im, phi, start, t, terms, t0, t1);
+    add_pauli_terms<R, U, true>(re, im, phi, start, t, terms, t1, t2);
+    double e = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint64_t i = start + 256u * u + t;
+        amps[lambda_base + off + i] = mk<R>((R)re[u], (R)im[u]);
+        const C2<R> p = phi[i];
+        e += (double)p.x * re[u] + (double)p.y * im[u];
+    }
+    return e;
+}
+
 template <typename R>
-__global__ __launch_bounds__(256) void k_batch_hamiltonian(C2<R> *__restrict__ amps, uint64_t lambda_base, BlockMap bm,
+__global__ __launch_bounds__(256) void k_batch_hamiltonian(C2<R> *__restrict__ amps, uint64_t lambda_base,
+                                                            const HBlock *__restrict__ blocks,
                                                             const uint64_t *__restrict__ offs,
                                                             const int *__restrict__ nq, const int *__restrict__ term_off,
-                                                            const DTerm *__restrict__ terms, double *__restrict__ epart)
+                                                            const PauliTerm *__restrict__ terms,
+                                                            double *__restrict__ epart)
 {
-    __shared__ double red[32];
-    const int c = bm.circ[blockIdx.x];
-    const uint64_t i = bm.start[blockIdx.x] + threadIdx.x;
-    double re = 0.0, im = 0.0;
-    if (i < (1ULL << nq[c])) {
-        const C2<R> *phi = amps + offs[c];
-        double lr = 0.0, li = 0.0;
-        const int tb = term_off[c], te = term_off[c + 1];
-        // indices within a circuit of at most 30 qubits: 32-bit
-        const uint32_t i32 = (uint32_t)i;
-        // a group's gathers in flight before their sums (same order of
-        // additions as one term at a time; the host pads every circuit's
-        // terms to whole groups with zero terms)
-        constexpr int G = kTermGroup;
-        for (int t0 = tb; t0 < te; t0 += G) {
-            C2<R> xs[G];
-#pragma unroll
-            for (int u = 0; u < G; u++) xs[u] = phi[i32 ^ (uint32_t)terms[t0 + u].x];
-#pragma unroll
-            for (int u = 0; u < G; u++) {
-                const DTerm tm = terms[t0 + u];
-                const uint32_t j = i32 ^ (uint32_t)tm.x;
-                const double s = (__popc(j & (uint32_t)tm.yz) & 1) ? -1.0 : 1.0;
-                const C2<R> x = xs[u];
-                lr += s * (tm.cre * x.x - tm.cim * x.y);
-                li += s * (tm.cre * x.y + tm.cim * x.x);
-            }
-        }
-        amps[lambda_base + offs[c] + i] = mk<R>((R)lr, (R)li);
-        const C2<R> p = phi[i];
-        re = (double)p.x * lr + (double)p.y * li;
-        im = (double)p.x * li - (double)p.y * lr;
-    }
-    bblock_sum2(re, im, red);
-    if (threadIdx.x == 0) {
-        epart[2 * blockIdx.x] = re;
-        epart[2 * blockIdx.x + 1] = im;
-    }
+    __shared__ double red[4];
+    const HBlock hb = blocks[blockIdx.x];
+    if (hb.circ < 0) return;   // the end of a shorter queue
+    const int c = hb.circ, n = nq[c];
+    const int t0 = term_off[2 * c], t1 = term_off[2 * c + 1], t2 = term_off[2 * c + 2];
+    double e = 0.0;
+    if (n >= 10)
+        e = hamiltonian_block<R, 4>(amps, lambda_base, offs[c], hb.start, terms, t0, t1, t2);
+    else if (hb.start + threadIdx.x < (1ULL << n))
+        e = hamiltonian_block<R, 1>(amps, lambda_base, offs[c], hb.start, terms, t0, t1, t2);
+    e = bwave_sum(e);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) epart[hb.part] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // One block per circuit: fixed-order sum of its blocks' energy partials.
 __global__ __launch_bounds__(256) void k_batch_energy(const double *__restrict__ epart, const int *__restrict__ first_block,
                                                        double *__restrict__ energy)
 {
-    __shared__ double red[32];
+    __shared__ double red[4];
     const int c = blockIdx.x;
-    double re = 0.0, im = 0.0;
-    for (int b = first_block[c] + threadIdx.x; b < first_block[c + 1]; b += blockDim.x) {
-        re += epart[2 * b];
-        im += epart[2 * b + 1];
-    }
-    bblock_sum2(re, im, red);
-    if (threadIdx.x == 0) {
-        energy[2 * c] = re;
-        energy[2 * c + 1] = im;
-    }
+    double e = 0.0;
+    for (int b = first_block[c] + threadIdx.x; b < first_block[c + 1]; b += blockDim.x) e += epart[b];
+    e = bwave_sum(e);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) energy[c] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// One thread per rotation: fixed-order sum over its tiles.
+// A wavefront per rotation: fixed-order sum over its tiles, times the
+// factors that its segment had left out there.
 __global__ __launch_bounds__(256) void k_batch_grad(const double *__restrict__ gpart, const uint64_t *__restrict__ first,
-                                                     int num_rot, double *__restrict__ out)
+                                                     const double *__restrict__ gscale, int num_rot,
+                                                     double *__restrict__ out)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    const int r = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     if (r >= num_rot) return;
     double im = 0.0;
-    for (uint64_t t = first[r]; t < first[r + 1]; t++) im += gpart[t];
-    out[r] = im;
+    for (uint64_t t = first[r] + (threadIdx.x & 63); t < first[r + 1]; t += 64) im += gpart[t];
+    im = bwave_sum(im);
+    if ((threadIdx.x & 63) == 0) out[r] = gscale[r] * im;
 }
 
 }  // namespace qs
@@ -482,15 +516,14 @@ struct qs_batch {
     DOp *d_ops = nullptr;
     std::vector<uint2 *> d_work;          // per phase
     std::vector<unsigned> phase_blocks;
-    int *d_bm_circ = nullptr;
-    uint64_t *d_bm_start = nullptr;
-    unsigned amp_blocks = 0;
-    int *d_init_blocks = nullptr;   // 256-amplitude blocks of the circuits without steps
+    HBlock *d_hblocks = nullptr;
+    unsigned h_blocks = 0;
+    int2 *d_init_blocks = nullptr;   // 256-amplitude blocks of the circuits without steps
     unsigned init_blocks = 0;
     uint64_t *d_offs = nullptr;
     int *d_nq = nullptr;
     int *d_term_off = nullptr;
-    DTerm *d_terms = nullptr;
+    PauliTerm *d_terms = nullptr;
     int *d_first_block = nullptr;
     double *d_epart = nullptr, *d_energy = nullptr, *h_energy = nullptr;
     double *d_gpart = nullptr, *d_gop = nullptr, *h_gop = nullptr;
@@ -499,7 +532,10 @@ struct qs_batch {
     std::vector<int> rot_param;      // global parameter of each rotation slot
     std::vector<double> rot_scale;
     double *d_params = nullptr, *h_params = nullptr;
-    double *d_trig = nullptr;   // cos, sin of every operator's angle
+    double *d_trig = nullptr;   // two values per operator (k_batch_trig)
+    DSeg *d_segs = nullptr;
+    int num_segs = 0;
+    double *d_scales = nullptr, *d_gscale = nullptr;   // factors of segments; of gradients
     std::vector<uint2 *> d_work_reg;          // register-path work lists per launch step
     std::vector<unsigned> phase_blocks_reg;
     BPhase *d_phases = nullptr;
@@ -572,25 +608,66 @@ static void plan_circuit(BCirc &c, int TQ, int C)
     }
 }
 
+// Order of the observable's blocks.  Blocks are handed to the 8 XCDs in turn,
+// each with an L2 of its own, and a term's gather reaches any block of the
+// circuit: in circuit order every XCD fetches nearly the whole state.  So
+// each circuit goes to one of 8 queues (the least loaded, largest first), and
+// block k of queue x is launched as block 8 k + x; a circuit of more than
+// half a queue's share is spread over all of them.  lambda = H psi of 192
+// circuits of 10-20 qubits, 20 terms each: 624 -> 504 us.
+static std::vector<HBlock> order_by_xcd(const std::vector<HBlock> &blocks, const std::vector<int> &first_block)
+{
+    constexpr int X = 8;
+    std::vector<std::vector<HBlock>> queue(X);
+    std::vector<int> order(first_block.size() - 1);
+    for (size_t c = 0; c < order.size(); c++) order[c] = (int)c;
+    auto size = [&](int c) { return (size_t)(first_block[(size_t)c + 1] - first_block[(size_t)c]); };
+    std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return size(p) > size(q); });
+    for (int c : order) {
+        const auto begin = blocks.begin() + first_block[(size_t)c];
+        if (size(c) * 2 * X > blocks.size()) {
+            for (size_t k = 0; k < size(c); k++) queue[k * X / size(c)].push_back(begin[(long)k]);
+            continue;
+        }
+        auto least = std::min_element(queue.begin(), queue.end(),
+                                      [](const auto &p, const auto &q) { return p.size() < q.size(); });
+        least->insert(least->end(), begin, begin + (long)size(c));
+    }
+    size_t longest = 0;
+    for (const auto &q : queue) longest = std::max(longest, q.size());
+    std::vector<HBlock> out;
+    for (size_t k = 0; k < longest; k++)
+        for (int x = 0; x < X; x++) out.push_back(k < queue[(size_t)x].size() ? queue[(size_t)x][k] : HBlock{-1, 0, 0});
+    return out;
+}
+
 static int launch_phase_kernels(qs_batch *b, bool grads)
 {
     const size_t ab = b->precision == QS_C64 ? 8 : 16;
     const size_t lds1 = ((size_t)1 << b->tile_qubits) * ab;
     const int P = (int)b->d_work.size();
-    hipLaunchKernelGGL(k_batch_trig, dim3((unsigned)((b->num_ops + 255) / 256)), dim3(256), 0, b->stream,
-                       (const DOp *)b->d_ops, b->num_ops, (const double *)b->d_params, b->d_trig);
-    QS_LAUNCH_CHECK();
+    if (b->num_segs > 0) {
+        const unsigned grid = (unsigned)((b->num_segs + 3) / 4);
+        if (b->precision == QS_C64)
+            hipLaunchKernelGGL(k_batch_trig<float>, dim3(grid), dim3(256), 0, b->stream, (const DSeg *)b->d_segs,
+                               b->num_segs, (const DOp *)b->d_ops, (const double *)b->d_params, b->d_trig, b->d_scales,
+                               b->d_gscale);
+        else
+            hipLaunchKernelGGL(k_batch_trig<double>, dim3(grid), dim3(256), 0, b->stream, (const DSeg *)b->d_segs,
+                               b->num_segs, (const DOp *)b->d_ops, (const double *)b->d_params, b->d_trig, b->d_scales,
+                               b->d_gscale);
+        QS_LAUNCH_CHECK();
+    }
     // |0..0> for circuits without operators (a circuit's first step reads
     // |0..0> itself)
     if (b->init_blocks > 0) {
         if (b->precision == QS_C64)
             hipLaunchKernelGGL(k_batch_init<float>, dim3(b->init_blocks), dim3(256), 0, b->stream, (float2 *)b->amps,
-                               BlockMap{b->d_bm_circ, b->d_bm_start}, (const int *)b->d_init_blocks,
-                               (const uint64_t *)b->d_offs, (const int *)b->d_nq);
+                               (const int2 *)b->d_init_blocks, (const uint64_t *)b->d_offs, (const int *)b->d_nq);
         else
             hipLaunchKernelGGL(k_batch_init<double>, dim3(b->init_blocks), dim3(256), 0, b->stream,
-                               (double2 *)b->amps, BlockMap{b->d_bm_circ, b->d_bm_start}, (const int *)b->d_init_blocks,
-                               (const uint64_t *)b->d_offs, (const int *)b->d_nq);
+                               (double2 *)b->amps, (const int2 *)b->d_init_blocks, (const uint64_t *)b->d_offs,
+                               (const int *)b->d_nq);
         QS_LAUNCH_CHECK();
     }
     const unsigned rblock = 1u << (b->tile_qubits - 3);   // register path: 8 amplitudes per thread
@@ -608,8 +685,8 @@ static int launch_phase_kernels(qs_batch *b, bool grads)
         }
         if (b->phase_blocks_reg[p] > 0 && p < (int)b->jit_fwd.size() && b->jit_fwd[p]) {
             void *amps = b->amps;
-            const void *steps = b->d_steps, *work = b->d_work_reg[p], *trig = b->d_trig;
-            void *args[] = {&amps, &steps, &work, &trig};
+            const void *steps = b->d_steps, *work = b->d_work_reg[p], *trig = b->d_trig, *scales = b->d_scales;
+            void *args[] = {&amps, &steps, &work, &trig, &scales};
             QS_HIP(hipModuleLaunchKernel((hipFunction_t)b->jit_fwd[p], b->phase_blocks_reg[p], 1, 1, rblock, 1, 1,
                                          (unsigned)lds1, b->stream, args, nullptr));
         } else if (b->phase_blocks_reg[p] > 0) {
@@ -617,24 +694,26 @@ static int launch_phase_kernels(qs_batch *b, bool grads)
                 hipLaunchKernelGGL(k_batch_forward_reg<float>, dim3(b->phase_blocks_reg[p]), dim3(rblock), lds1,
                                    b->stream, (float2 *)b->amps, (const DStep *)b->d_steps,
                                    (const BPhase *)b->d_phases, (const DOp *)b->d_ops,
-                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig);
+                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig,
+                                   (const double *)b->d_scales);
             else
                 hipLaunchKernelGGL(k_batch_forward_reg<double>, dim3(b->phase_blocks_reg[p]), dim3(rblock), lds1,
                                    b->stream, (double2 *)b->amps, (const DStep *)b->d_steps,
                                    (const BPhase *)b->d_phases, (const DOp *)b->d_ops,
-                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig);
+                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig,
+                                   (const double *)b->d_scales);
             QS_LAUNCH_CHECK();
         }
     }
-    const BlockMap bm{b->d_bm_circ, b->d_bm_start};
     if (b->precision == QS_C64)
-        hipLaunchKernelGGL(k_batch_hamiltonian<float>, dim3(b->amp_blocks), dim3(256), 0, b->stream, (float2 *)b->amps,
-                           b->total_amps, bm, (const uint64_t *)b->d_offs, (const int *)b->d_nq,
-                           (const int *)b->d_term_off, (const DTerm *)b->d_terms, b->d_epart);
+        hipLaunchKernelGGL(k_batch_hamiltonian<float>, dim3(b->h_blocks), dim3(256), 0, b->stream, (float2 *)b->amps,
+                           b->total_amps, (const HBlock *)b->d_hblocks, (const uint64_t *)b->d_offs,
+                           (const int *)b->d_nq, (const int *)b->d_term_off, (const PauliTerm *)b->d_terms, b->d_epart);
     else
-        hipLaunchKernelGGL(k_batch_hamiltonian<double>, dim3(b->amp_blocks), dim3(256), 0, b->stream,
-                           (double2 *)b->amps, b->total_amps, bm, (const uint64_t *)b->d_offs, (const int *)b->d_nq,
-                           (const int *)b->d_term_off, (const DTerm *)b->d_terms, b->d_epart);
+        hipLaunchKernelGGL(k_batch_hamiltonian<double>, dim3(b->h_blocks), dim3(256), 0, b->stream,
+                           (double2 *)b->amps, b->total_amps, (const HBlock *)b->d_hblocks,
+                           (const uint64_t *)b->d_offs, (const int *)b->d_nq, (const int *)b->d_term_off,
+                           (const PauliTerm *)b->d_terms, b->d_epart);
     QS_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_batch_energy, dim3((unsigned)b->circs.size()), dim3(256), 0, b->stream,
                        (const double *)b->d_epart, (const int *)b->d_first_block, b->d_energy);
@@ -657,8 +736,8 @@ static int launch_phase_kernels(qs_batch *b, bool grads)
         if (b->phase_blocks_reg[p] > 0 && p < (int)b->jit_bwd.size() && b->jit_bwd[p]) {
             void *amps = b->amps, *gpart = b->d_gpart;
             unsigned long long lambda_base = b->total_amps;
-            const void *steps = b->d_steps, *ops = b->d_ops, *work = b->d_work_reg[p], *trig = b->d_trig;
-            void *args[] = {&amps, &lambda_base, &steps, &ops, &work, &trig, &gpart};
+            const void *steps = b->d_steps, *work = b->d_work_reg[p], *trig = b->d_trig, *scales = b->d_scales;
+            void *args[] = {&amps, &lambda_base, &steps, &work, &trig, &scales, &gpart};
             QS_HIP(hipModuleLaunchKernel((hipFunction_t)b->jit_bwd[p], b->phase_blocks_reg[p], 1, 1, rblock, 1, 1,
                                          (unsigned)(2 * lds1), b->stream, args, nullptr));
         } else if (b->phase_blocks_reg[p] > 0) {
@@ -666,18 +745,21 @@ static int launch_phase_kernels(qs_batch *b, bool grads)
                 hipLaunchKernelGGL(k_batch_backward_reg<float>, dim3(b->phase_blocks_reg[p]), dim3(rblock),
                                    2 * lds1, b->stream, (float2 *)b->amps, b->total_amps,
                                    (const DStep *)b->d_steps, (const BPhase *)b->d_phases, (const DOp *)b->d_ops,
-                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig, b->d_gpart);
+                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig,
+                                   (const double *)b->d_scales, b->d_gpart);
             else
                 hipLaunchKernelGGL(k_batch_backward_reg<double>, dim3(b->phase_blocks_reg[p]), dim3(rblock),
                                    2 * lds1, b->stream, (double2 *)b->amps, b->total_amps,
                                    (const DStep *)b->d_steps, (const BPhase *)b->d_phases, (const DOp *)b->d_ops,
-                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig, b->d_gpart);
+                                   (const uint2 *)b->d_work_reg[p], (const double *)b->d_trig,
+                                   (const double *)b->d_scales, b->d_gpart);
             QS_LAUNCH_CHECK();
         }
     }
     if (b->num_rot > 0) {
-        hipLaunchKernelGGL(k_batch_grad, dim3((b->num_rot + 255) / 256), dim3(256), 0, b->stream,
-                           (const double *)b->d_gpart, (const uint64_t *)b->d_gfirst, b->num_rot, b->d_gop);
+        hipLaunchKernelGGL(k_batch_grad, dim3((b->num_rot + 3) / 4), dim3(256), 0, b->stream,
+                           (const double *)b->d_gpart, (const uint64_t *)b->d_gfirst, (const double *)b->d_gscale,
+                           b->num_rot, b->d_gop);
         QS_LAUNCH_CHECK();
     }
     return QS_OK;
@@ -745,8 +827,7 @@ static void release(qs_batch *b)
     b->phase_blocks_reg.clear();
     f(b->d_phases);
     b->d_phases = nullptr;
-    f(b->d_bm_circ);
-    f(b->d_bm_start);
+    f(b->d_hblocks);
     f(b->d_init_blocks);
     b->d_init_blocks = nullptr;
     b->init_blocks = 0;
@@ -762,14 +843,19 @@ static void release(qs_batch *b)
     f(b->d_gfirst);
     f(b->d_params);
     f(b->d_trig);
+    f(b->d_segs);
+    f(b->d_scales);
+    f(b->d_gscale);
+    b->d_segs = nullptr;
+    b->d_scales = b->d_gscale = nullptr;
+    b->num_segs = 0;
     if (b->h_energy) (void)hipHostFree(b->h_energy);
     if (b->h_gop) (void)hipHostFree(b->h_gop);
     if (b->h_params) (void)hipHostFree(b->h_params);
     b->amps = nullptr;
     b->d_steps = nullptr;
     b->d_ops = nullptr;
-    b->d_bm_circ = nullptr;
-    b->d_bm_start = nullptr;
+    b->d_hblocks = nullptr;
     b->d_offs = nullptr;
     b->d_nq = nullptr;
     b->d_term_off = nullptr;
@@ -818,13 +904,6 @@ static std::string dop_init(const DOp &o)
     return s.str();
 }
 
-static bool phase_has_grads(const qs_batch *b, const BPhase &P)
-{
-    for (int k = P.op_begin; k < P.op_end; k++)
-        if (b->h_ops[k].grad >= 0) return true;
-    return false;
-}
-
 // Program key of register-path step si: everything its generated code
 // depends on.
 static std::string program_key(const qs_batch *b, int si)
@@ -835,7 +914,8 @@ static std::string program_key(const qs_batch *b, int si)
     for (int p = st.ph_begin; p < st.ph_end; p++) {
         const BPhase &P = b->h_phases[p];
         k << "P" << P.lo[0] << "," << P.lo[1] << "," << P.lo[2] << "," << P.rc[0] << "," << P.rc[1] << ","
-          << P.rc[2] << "," << P.op_begin - st.op_begin << "," << P.op_end - st.op_begin << ";";
+          << P.rc[2] << "," << P.op_begin - st.op_begin << "," << P.op_end - st.op_begin << "," << P.fscale << ","
+          << P.bscale << "," << P.rot_begin << "," << P.rots << ";";
         for (int j = P.op_begin; j < P.op_end; j++) k << dop_init(b->h_ops[j]) << ";";
     }
     return k.str();
@@ -851,17 +931,28 @@ static void program_source(std::ostringstream &o, const qs_batch *b, int id, int
         const BPhase &P = b->h_phases[st.ph_begin + k];
         ph << "    constexpr qs::BPhase P" << k << " = {{" << P.lo[0] << "u, " << P.lo[1] << "u, " << P.lo[2]
            << "u}, {" << P.rc[0] << ", " << P.rc[1] << ", " << P.rc[2] << "}, " << P.op_begin - st.op_begin << ", "
-           << P.op_end - st.op_begin << "};\n";
+           << P.op_end - st.op_begin << ", " << P.fscale << ", " << P.bscale << ", " << P.rot_begin << ", "
+           << P.rots << "};\n";
     }
     auto op_line = [&](int j, const char *call) {
         o << "        { constexpr qs::DOp O = " << dop_init(b->h_ops[j]) << "; " << call << "(x, "
-          << (bwd ? "y, " : "") << "O, st.op_begin + " << j - st.op_begin << ", trig, tau, base, czm"
-          << (bwd ? ", red, lane, wave" : "") << "); }\n";
+          << (bwd ? "y, " : "") << "O, ";
+        if (b->h_ops[j].kind == BOP_ROT) o << "m" << j - st.op_begin;
+        else o << "qs::RotM<R>{}";
+        o << ", tau, base, czm" << (bwd ? ", red, lane, wave" : "") << "); }\n";
+    };
+    // a phase's table entries, loaded together ahead of its exchange (one by
+    // one, each rotation's branch would wait for its own)
+    auto load_rots = [&](const BPhase &P) {
+        for (int j = P.op_begin; j < P.op_end; j++)
+            if (b->h_ops[j].kind == BOP_ROT)
+                o << "    const qs::RotM<R> m" << j - st.op_begin << " = qs::load_rot<R>(trig, st.op_begin + "
+                  << j - st.op_begin << ");\n";
     };
     if (!bwd) {
         o << "template <typename R>\n__device__ __forceinline__ void bfwd_" << id
           << "(qs::C2<R> *__restrict__ amps, const qs::DStep &st, uint64_t base, const double *__restrict__ trig, "
-             "unsigned char *lds)\n{\n"
+             "const double *__restrict__ scales, unsigned char *lds)\n{\n"
           << ph.str();
         o << "    qs::C2<R> *v = reinterpret_cast<qs::C2<R> *>(lds);\n    qs::C2<R> *a = amps + st.amp_off;\n";
         o << "    const bool active = threadIdx.x < " << nthr << "u;\n";
@@ -871,9 +962,11 @@ static void program_source(std::ostringstream &o, const qs_batch *b, int id, int
              "        for (int u = 0; u < 8; u++) x[u] = qs::load_amp<R>(a, xo | ro(u), st.first);\n    }\n";
         for (int k = 0; k < np; k++) {
             const BPhase &P = b->h_phases[st.ph_begin + k];
+            load_rots(P);
             if (k) o << "    tau = qs::bphase_exchange<R>(x, v, tau, P" << k - 1 << ", P" << k << ", active);\n";
             o << "    if (active) {\n        uint32_t czm = 0;\n";
             for (int j = P.op_begin; j < P.op_end; j++) op_line(j, "qs::fwd_op<R>");
+            if (P.fscale >= 0) o << "        qs::reg_scale8<R>(x, scales[2 * (st.seg_begin + " << P.fscale << ")]);\n";
             o << "        (void)czm;\n    }\n";
         }
         o << "    if (active) {\n        const uint64_t xo = base | qs::tile_offset_bits(tau, st);\n"
@@ -883,8 +976,8 @@ static void program_source(std::ostringstream &o, const qs_batch *b, int id, int
     }
     o << "template <typename R>\n__device__ __forceinline__ void bbwd_" << id
       << "(qs::C2<R> *__restrict__ amps, uint64_t lambda_base, const qs::DStep &st, uint32_t tile, uint64_t base, "
-         "const qs::DOp *__restrict__ ops, const double *__restrict__ trig, double *__restrict__ gpart, "
-         "unsigned char *lds, double (*red)[qs::kRedRows])\n{\n"
+         "const double *__restrict__ trig, const double *__restrict__ scales, "
+         "double *__restrict__ gpart, unsigned char *lds, double (*red)[qs::kRedRows])\n{\n"
       << ph.str();
     o << "    qs::C2<R> *vphi = reinterpret_cast<qs::C2<R> *>(lds);\n    qs::C2<R> *vlam = vphi + " << (1u << st.qn)
       << ";\n    qs::C2<R> *a = amps + st.amp_off;\n    qs::C2<R> *l = amps + lambda_base + st.amp_off;\n";
@@ -897,13 +990,12 @@ static void program_source(std::ostringstream &o, const qs_batch *b, int id, int
       << ", st);\n#pragma unroll\n        for (int u = 0; u < 8; u++) {\n            const uint64_t o = xo | ro(u);\n"
          "            x[u] = a[o];\n            y[u] = l[o];\n        }\n    }\n";
     auto flush = [&](int k) {
-        const BPhase &D = b->h_phases[st.ph_begin + k];
-        if (phase_has_grads(b, D))
-            o << "    qs::flush_phase(ops, st.op_begin + " << D.op_begin - st.op_begin << ", st.op_begin + "
-              << D.op_end - st.op_begin << ", red, " << (nthr >> 6) << ", tile, gpart);\n";
+        if (b->h_phases[st.ph_begin + k].rots > 0)
+            o << "    qs::flush_phase(P" << k << ", st, red, " << (nthr >> 6) << ", tile, gpart);\n";
     };
     for (int k = np - 1; k >= 0; k--) {
         const BPhase &P = b->h_phases[st.ph_begin + k];
+        load_rots(P);
         if (k < np - 1) {
             o << "    __syncthreads();\n";
             flush(k + 1);
@@ -911,6 +1003,9 @@ static void program_source(std::ostringstream &o, const qs_batch *b, int id, int
         }
         o << "    if (active) {\n        uint32_t czm = 0;\n";
         for (int j = P.op_end - 1; j >= P.op_begin; j--) op_line(j, "qs::bwd_op<R>");
+        if (P.bscale >= 0)
+            o << "        const double f = scales[2 * (st.seg_begin + " << P.bscale << ") + 1];\n"
+              << "        qs::reg_scale8<R>(x, f);\n        qs::reg_scale8<R>(y, f);\n";
         o << "        (void)czm;\n    }\n";
     }
     o << "    __syncthreads();\n";
@@ -933,22 +1028,22 @@ static std::string launch_source(const qs_batch *b, int s, const std::vector<std
     if (!bwd) {
         o << "extern \"C\" __global__ __launch_bounds__(512) void qs_bfwd_" << s << "(" << c2
           << " *__restrict__ amps, const qs::DStep *__restrict__ steps, const uint2 *__restrict__ work, "
-             "const double *__restrict__ trig)\n{\n";
+             "const double *__restrict__ trig, const double *__restrict__ scales)\n{\n";
     } else {
         o << "extern \"C\" __global__ __launch_bounds__(512) void qs_bbwd_" << s << "(" << c2
           << " *__restrict__ amps, unsigned long long lambda_base, const qs::DStep *__restrict__ steps, "
-             "const qs::DOp *__restrict__ ops, const uint2 *__restrict__ work, const double *__restrict__ trig, "
-             "double *__restrict__ gpart)\n{\n    __shared__ double red[qs::kPhaseRotMax][qs::kRedRows];\n";
+             "const uint2 *__restrict__ work, const double *__restrict__ trig, "
+             "const double *__restrict__ scales, double *__restrict__ gpart)\n{\n    __shared__ double red[qs::kPhaseRotMax][qs::kRedRows];\n";
     }
     o << "    using R = " << (f32 ? "float" : "double") << ";\n    extern __shared__ unsigned char lds_raw[];\n";
     o << "    const uint2 w = work[blockIdx.x];\n    const qs::DStep &st = steps[w.x];\n"
          "    const uint64_t base = qs::insert_zeros(w.y, st.plan);\n    switch (st.prog) {\n";
     for (const auto &pr : progs) {
         if (!bwd)
-            o << "    case " << pr.first << ": bfwd_" << pr.first << "<R>(amps, st, base, trig, lds_raw); break;\n";
+            o << "    case " << pr.first << ": bfwd_" << pr.first << "<R>(amps, st, base, trig, scales, lds_raw); break;\n";
         else
             o << "    case " << pr.first << ": bbwd_" << pr.first
-              << "<R>(amps, lambda_base, st, w.y, base, ops, trig, gpart, lds_raw, red); break;\n";
+              << "<R>(amps, lambda_base, st, w.y, base, trig, scales, gpart, lds_raw, red); break;\n";
     }
     o << "    default: break;\n    }\n}\n";
     return o.str();
@@ -1330,6 +1425,7 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
     std::vector<DStep> steps;
     std::vector<DOp> ops;
     std::vector<BPhase> phases;
+    std::vector<DSeg> segs;
     b->step_launch.clear();
     std::vector<uint64_t> gfirst{0};
     b->rot_param.clear();
@@ -1371,13 +1467,6 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
                 }
                 x.grad = -1;
                 x.rbit = x.rbit1 = -1;
-                if (o.kind == BOP_ROT) {
-                    x.grad = (int)b->rot_param.size();
-                    x.gpart = gfirst.back();
-                    gfirst.push_back(gfirst.back() + tiles);
-                    b->rot_param.push_back(c.param_off + o.param);
-                    b->rot_scale.push_back(o.scale);
-                }
                 ops.push_back(x);
             }
             d.op_end = (int)ops.size();
@@ -1389,6 +1478,7 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
                 // remaining operator it jumps over (the step's operators are
                 // regrouped by phase)
                 std::vector<DOp> seg(ops.begin() + d.op_begin, ops.begin() + d.op_end), out;
+                int step_rots = 0;
                 std::vector<char> used(seg.size(), 0);
                 auto support = [](const DOp &x) {
                     return (1ULL << x.q0) | (x.kind == BOP_CZ ? (1ULL << x.q1) : 0ULL);
@@ -1464,10 +1554,53 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
                         }
                         std::copy(ord.begin(), ord.end(), out.begin() + (long)first);
                     }
+                    ph.fscale = ph.bscale = -1;
+                    ph.rot_begin = step_rots;
+                    ph.rots = nrot;
+                    step_rots += nrot;
                     phases.push_back(ph);
                 }
                 std::copy(out.begin(), out.end(), ops.begin() + d.op_begin);
                 d.ph_end = (int)phases.size();
+                // segments: whole phases, closed at kSegmentRots rotations
+                d.seg_begin = (int)segs.size();
+                int from = d.ph_begin, rots = 0;
+                for (int p = d.ph_begin; p < d.ph_end; p++) {
+                    for (int k = phases[p].op_begin; k < phases[p].op_end; k++) rots += ops[k].kind == BOP_ROT;
+                    if (rots < kSegmentRots && p + 1 < d.ph_end) continue;
+                    if (rots > 0) {
+                        phases[p].fscale = phases[from].bscale = (int)segs.size() - d.seg_begin;
+                        segs.push_back({phases[from].op_begin, phases[p].op_end, 1});
+                    }
+                    from = p + 1;
+                    rots = 0;
+                }
+            } else if (d.op_end > d.op_begin) {
+                segs.push_back({d.op_begin, d.op_end, 0});
+            }
+            // a gradient slot and a row of partials (one per tile) for every
+            // rotation: by phase and slot within it (rotations keep their
+            // slots' order there), or by operator
+            d.gpart = gfirst.back();
+            d.tiles = tiles;
+            std::vector<int> rot_ops;
+            if (d.ph_end > d.ph_begin) {
+                for (int p = d.ph_begin; p < d.ph_end; p++) {
+                    const size_t at = rot_ops.size();
+                    rot_ops.resize(at + (size_t)phases[p].rots);
+                    for (int k = phases[p].op_begin; k < phases[p].op_end; k++)
+                        if (ops[k].kind == BOP_ROT) rot_ops[at + (size_t)ops[k].slot] = k;
+                }
+            } else {
+                for (int k = d.op_begin; k < d.op_end; k++)
+                    if (ops[k].kind == BOP_ROT) rot_ops.push_back(k);
+            }
+            for (int k : rot_ops) {
+                ops[k].grad = (int)b->rot_param.size();
+                ops[k].gpart = gfirst.back();
+                gfirst.push_back(gfirst.back() + tiles);
+                b->rot_param.push_back(ops[k].param);
+                b->rot_scale.push_back(ops[k].scale);
             }
             step_index[ci].push_back((int)steps.size());
             b->step_launch.push_back((int)step_index[ci].size() - 1);
@@ -1488,44 +1621,46 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
         }
     }
 
-    // 256-amplitude block map, observables
-    std::vector<int> bm_circ, first_block, nq, term_off{0};
-    std::vector<uint64_t> bm_start, offs;
-    std::vector<DTerm> terms;
-    const cd eta[4] = {cd(1, 0), cd(0, 1), cd(-1, 0), cd(0, -1)};
+    // blocks of the observable kernel, observables
+    std::vector<HBlock> hblocks;
+    std::vector<int> first_block, nq, term_off{0};
+    std::vector<uint64_t> offs;
+    std::vector<PauliTerm> terms;
+    std::vector<int2> init_blocks;
     for (size_t ci = 0; ci < b->circs.size(); ci++) {
         const BCirc &c = b->circs[ci];
-        first_block.push_back((int)bm_circ.size());
-        for (uint64_t s = 0; s < (1ULL << c.n); s += 256) {
-            bm_circ.push_back((int)ci);
-            bm_start.push_back(s);
-        }
+        first_block.push_back((int)hblocks.size());
+        const uint64_t per = c.n >= 10 ? 1024 : 256;
+        for (uint64_t s = 0; s < (1ULL << c.n); s += per)
+            hblocks.push_back(HBlock{(int)ci, (int)hblocks.size(), s});
+        if (c.steps.empty())
+            for (uint64_t k = 0; k << 8 < (1ULL << c.n); k++) init_blocks.push_back(make_int2((int)ci, (int)k));
         offs.push_back(c.amp_off);
         nq.push_back(c.n);
-        const int T = (int)c.coeffs.size();
-        for (int t = 0; t < T; t++) {
-            DTerm d{};
-            int ny = 0;
-            for (int q = 0; q < c.n; q++) {
-                const int code = c.codes[(size_t)t * c.n + q];
-                if (code == 1 || code == 2) d.x |= 1ULL << q;
-                if (code == 2 || code == 3) d.yz |= 1ULL << q;
-                if (code == 2) ny++;
+        // i^{#Y} h P: real coefficients first, then imaginary ones, each padded
+        // with zero terms to whole groups of the gather
+        for (int odd = 0; odd < 2; odd++) {
+            for (int t = 0; t < (int)c.coeffs.size(); t++) {
+                PauliTerm d{};
+                int ny = 0;
+                for (int q = 0; q < c.n; q++) {
+                    const int code = c.codes[(size_t)t * c.n + q];
+                    if (code == 1 || code == 2) d.x |= 1ULL << q;
+                    if (code == 2 || code == 3) d.yz |= 1ULL << q;
+                    if (code == 2) ny++;
+                }
+                if ((ny & 1) != odd) continue;
+                d.c = (ny & 2) ? -c.coeffs[t] : c.coeffs[t];
+                terms.push_back(d);
             }
-            const cd cf = c.coeffs[t] * eta[ny & 3];
-            d.cre = cf.real();
-            d.cim = cf.imag();
-            terms.push_back(d);
+            while ((terms.size() - (size_t)term_off.back()) % kTermGroup) terms.push_back(PauliTerm{});
+            term_off.push_back((int)terms.size());
         }
-        // padded with zero terms to whole groups of the gather kernel
-        while ((terms.size() - (size_t)term_off.back()) % kTermGroup) terms.push_back(DTerm{});
-        term_off.push_back((int)terms.size());
     }
-    first_block.push_back((int)bm_circ.size());
-    b->amp_blocks = (unsigned)bm_circ.size();
-    std::vector<int> init_blocks;
-    for (size_t k = 0; k < bm_circ.size(); k++)
-        if (b->circs[(size_t)bm_circ[k]].steps.empty()) init_blocks.push_back((int)k);
+    first_block.push_back((int)hblocks.size());
+    const size_t num_parts = hblocks.size();
+    hblocks = order_by_xcd(hblocks, first_block);
+    b->h_blocks = (unsigned)hblocks.size();
     b->init_blocks = (unsigned)init_blocks.size();
 
     int rc = QS_OK;
@@ -1539,8 +1674,7 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
     }
     up(&b->d_steps, steps);
     up(&b->d_ops, ops);
-    up(&b->d_bm_circ, bm_circ);
-    up(&b->d_bm_start, bm_start);
+    up(&b->d_hblocks, hblocks);
     up(&b->d_init_blocks, init_blocks);
     up(&b->d_offs, offs);
     up(&b->d_nq, nq);
@@ -1564,18 +1698,22 @@ int qs_batch_compile(qs_batch *b, void *hip_stream, int use_graph)
         b->phase_blocks_reg.push_back((unsigned)w.size());
     }
     up(&b->d_phases, phases);
+    up(&b->d_segs, segs);
+    b->num_segs = (int)segs.size();
     b->h_steps = steps;
     b->h_ops = ops;
     b->h_phases = phases;
     if (rc != QS_OK) return rc;
-    if ((rc = upload(&b->d_epart, nullptr, sizeof(double) * 2 * bm_circ.size())) != QS_OK) return rc;
-    if ((rc = upload(&b->d_energy, nullptr, sizeof(double) * 2 * b->circs.size())) != QS_OK) return rc;
+    if ((rc = upload(&b->d_epart, nullptr, sizeof(double) * num_parts)) != QS_OK) return rc;
+    if ((rc = upload(&b->d_energy, nullptr, sizeof(double) * b->circs.size())) != QS_OK) return rc;
     if ((rc = upload(&b->d_gpart, nullptr, sizeof(double) * std::max<uint64_t>(1, gfirst.back()))) != QS_OK) return rc;
     if ((rc = upload(&b->d_gop, nullptr, sizeof(double) * std::max(1, b->num_rot))) != QS_OK) return rc;
     if ((rc = upload(&b->d_params, nullptr, sizeof(double) * std::max(1, b->total_params))) != QS_OK) return rc;
     b->num_ops = (int)ops.size();
     if ((rc = upload(&b->d_trig, nullptr, sizeof(double) * 2 * std::max(1, b->num_ops))) != QS_OK) return rc;
-    if (hipHostMalloc(&b->h_energy, sizeof(double) * 2 * b->circs.size(), hipHostMallocDefault) != hipSuccess ||
+    if ((rc = upload(&b->d_scales, nullptr, sizeof(double) * 2 * std::max(1, b->num_segs))) != QS_OK) return rc;
+    if ((rc = upload(&b->d_gscale, nullptr, sizeof(double) * std::max(1, b->num_rot))) != QS_OK) return rc;
+    if (hipHostMalloc(&b->h_energy, sizeof(double) * b->circs.size(), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(&b->h_gop, sizeof(double) * std::max(1, b->num_rot), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(&b->h_params, sizeof(double) * std::max(1, b->total_params), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -1607,13 +1745,13 @@ int qs_batch_run(qs_batch *b, const double *params, double *energies, double *gr
         int rc = launch_phase_kernels(b, want_grads);
         if (rc != QS_OK) return rc;
     }
-    QS_HIP(hipMemcpyAsync(b->h_energy, b->d_energy, sizeof(double) * 2 * b->circs.size(), hipMemcpyDeviceToHost,
+    QS_HIP(hipMemcpyAsync(b->h_energy, b->d_energy, sizeof(double) * b->circs.size(), hipMemcpyDeviceToHost,
                           b->stream));
     if (want_grads && b->num_rot > 0)
         QS_HIP(hipMemcpyAsync(b->h_gop, b->d_gop, sizeof(double) * b->num_rot, hipMemcpyDeviceToHost, b->stream));
     QS_HIP(hipStreamSynchronize(b->stream));
     if (energies)
-        for (size_t c = 0; c < b->circs.size(); c++) energies[c] = b->h_energy[2 * c];
+        for (size_t c = 0; c < b->circs.size(); c++) energies[c] = b->h_energy[c];
     if (want_grads) {
         for (int p = 0; p < b->total_params; p++) grads[p] = 0.0;
         // dE/dtheta_p += 2 Re(i scale <lambda|P|phi>) = -2 scale Im<lambda|P|phi>

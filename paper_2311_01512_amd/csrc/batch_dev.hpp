@@ -40,6 +40,9 @@ struct DStep {
     int qpos[kTileMax];
     int op_begin, op_end;
     int ph_begin, ph_end;   // register phases (steps of >= kRegMinQubits qubits)
+    int seg_begin;          // first of the step's segments in the scale table
+    uint64_t gpart;         // gradient partials of a register-path step: row r (a rotation) and tile t
+    uint64_t tiles;         // at gpart + r tiles + t
     int prog;               // specialised step program of a register-path step (-1: none)
     int first;              // step 0 of its circuit: reads |0..0> instead of the state
 };
@@ -67,7 +70,40 @@ struct BPhase {
     uint32_t lo[3];                  // (1 << rc) - 1, ascending
     int rc[3];                       // coordinate of register bit j
     int op_begin, op_end;
+    int fscale, bscale;              // segment that ends with this phase in the forward / backward
+                                     // direction (its number in the step), or -1
+    int rot_begin, rots;             // its rotations: the step's gradient rows rot_begin + slot
 };
+
+// Rotations on the register path run with a factor taken out: with
+// c = cos(theta), s = sin(theta),
+//   c 1 + i s P = c (1 + i m P), m = s / c   where |c| >= |s| (form 1),
+//               = s (m + i P),   m = c / s   otherwise (form 0),
+// one FMA per real component instead of a product and an FMA.  The factors are
+// real numbers that every amplitude of the state gets alike, so they wait for
+// the end of a segment (a few phases of a step, kSegmentRots rotations or a
+// little more), where one multiplication applies their product, formed in FP64
+// once per run.  Until then registers hold up to sqrt(2) per rotation too
+// much, which neither precision's range notices.
+// Two doubles per operator in the table trig: m and the form of a
+// register-path rotation (RotM; cos and sin in steps without phases).  scales[2 g], scales[2 g + 1]: the factor
+// of segment g forward and backward (the adjoint has -s in the place of s).
+// (Half the arithmetic alone took the forward steps of 192 circuits of 10-20
+// qubits from 0.95 to 0.92 ms and the backward steps from 3.71 to 3.47 ms: the
+// exchanges bounded them, see tile_slot.)
+constexpr int kSegmentRots = 32;
+
+// A register-path rotation's table entry.
+template <typename R> struct RotM {
+    R m;
+    uint32_t form;
+};
+
+template <typename R>
+__device__ __forceinline__ RotM<R> load_rot(const double *__restrict__ trig, int k)
+{
+    return *reinterpret_cast<const RotM<R> *>(trig + 2 * k);
+}
 
 // v moved across lanes by a DPP control (both 32-bit halves); lanes of rows
 // outside row_mask receive 0.
@@ -143,9 +179,9 @@ __device__ __forceinline__ double brow_sum(double v)
 // wavefront, 8 wavefronts at most) and gradient slot.
 constexpr int kRedRows = 32;
 
-// 2 x 2 matrix of an operator; dir = -1 gives its adjoint.  A rotation's
-// cos and sin come from the per-operator table trig (filled by k_batch_trig
-// for the current parameters), not from a per-lane sincos.
+// 2 x 2 matrix of an operator (rotations: of steps without phases, whose cos
+// and sin come from the table trig that k_batch_trig fills for the current
+// parameters, not from a per-lane sincos); dir = -1 gives its adjoint.
 template <typename R>
 __device__ __forceinline__ void op_matrix(const DOp &op, const double *trig, int dir, C2<R> (&u)[4])
 {
@@ -250,53 +286,73 @@ __device__ __forceinline__ double reg_grad_pairs(const C2<R> (&x)[8], const C2<R
     return im;
 }
 
-// Rotation c 1 + i s P (P = X, Y, Z by PA = 1, 2, 3) on the register pairs
-// (u0, u0 | 1 << J): the matrix's zeros and its real or imaginary entries
-// spelled out, 8 FP operations per pair instead of a general 2 x 2
-// complex product's 16.  Explicit FMAs (no implicit contraction), so that
-// the generic kernels and the specialised ones round alike.
-template <typename R, int J, int PA>
-__device__ __forceinline__ void reg_rot_pairs(C2<R> (&x)[8], R c, R s)
+// Rotation exp(i theta P) (P = X, Y, Z by PA = 1, 2, 3) without its factor on
+// the register pairs (u0, u0 | 1 << J): 1 + i m P (FORM 1) or m + i P.
+// Explicit FMAs (no implicit contraction), so that the generic kernels and
+// the specialised ones round alike.
+template <typename R, int J, int PA, int FORM>
+__device__ __forceinline__ void reg_rot_pairs(C2<R> (&x)[8], R m)
 {
 #pragma clang fp contract(off)
+    // p + q, one of the two times m
+    auto mix = [&](R p, R q) { return FORM ? fma(m, q, p) : fma(m, p, q); };
 #pragma unroll
     for (int u0 = 0; u0 < 8; u0++) {
         if ((u0 >> J) & 1) continue;
         const C2<R> a = x[u0], b = x[u0 | (1 << J)];
-        if constexpr (PA == 1) {          // (c a + i s b, i s a + c b)
-            x[u0] = mk<R>(fma(c, a.x, -(s * b.y)), fma(c, a.y, s * b.x));
-            x[u0 | (1 << J)] = mk<R>(fma(c, b.x, -(s * a.y)), fma(c, b.y, s * a.x));
-        } else if constexpr (PA == 2) {   // (c a + s b, c b - s a)
-            x[u0] = mk<R>(fma(c, a.x, s * b.x), fma(c, a.y, s * b.y));
-            x[u0 | (1 << J)] = mk<R>(fma(c, b.x, -(s * a.x)), fma(c, b.y, -(s * a.y)));
-        } else {                          // ((c + i s) a, (c - i s) b)
-            x[u0] = mk<R>(fma(c, a.x, -(s * a.y)), fma(c, a.y, s * a.x));
-            x[u0 | (1 << J)] = mk<R>(fma(c, b.x, s * b.y), fma(c, b.y, -(s * b.x)));
+        if constexpr (PA == 1) {          // i X: (i b, i a)
+            x[u0] = mk<R>(mix(a.x, -b.y), mix(a.y, b.x));
+            x[u0 | (1 << J)] = mk<R>(mix(b.x, -a.y), mix(b.y, a.x));
+        } else if constexpr (PA == 2) {   // i Y: (b, -a)
+            x[u0] = mk<R>(mix(a.x, b.x), mix(a.y, b.y));
+            x[u0 | (1 << J)] = mk<R>(mix(b.x, -a.x), mix(b.y, -a.y));
+        } else {                          // i Z: (i a, -i b)
+            x[u0] = mk<R>(mix(a.x, -a.y), mix(a.y, a.x));
+            x[u0 | (1 << J)] = mk<R>(mix(b.x, b.y), mix(b.y, -b.x));
         }
     }
     // distinct empty statements, as in reg_pairs
-    if constexpr (J == 0) asm volatile("; rot pairs 0");
-    else if constexpr (J == 1) asm volatile("; rot pairs 1");
-    else asm volatile("; rot pairs 2");
+    if constexpr (J == 0) asm volatile("; rot pairs 0 %0" ::"n"(FORM));
+    else if constexpr (J == 1) asm volatile("; rot pairs 1 %0" ::"n"(FORM));
+    else asm volatile("; rot pairs 2 %0" ::"n"(FORM));
 }
 
-template <typename R, int PA>
-__device__ __forceinline__ void reg_rot_p(C2<R> (&x)[8], int rbit, R c, R s)
+template <typename R, int PA, int FORM>
+__device__ __forceinline__ void reg_rot_p(C2<R> (&x)[8], int rbit, R m)
 {
     switch (rbit) {
-    case 0: reg_rot_pairs<R, 0, PA>(x, c, s); break;
-    case 1: reg_rot_pairs<R, 1, PA>(x, c, s); break;
-    default: reg_rot_pairs<R, 2, PA>(x, c, s); break;
+    case 0: reg_rot_pairs<R, 0, PA, FORM>(x, m); break;
+    case 1: reg_rot_pairs<R, 1, PA, FORM>(x, m); break;
+    default: reg_rot_pairs<R, 2, PA, FORM>(x, m); break;
     }
 }
 
-// A rotation exp(i theta P) (s = dir sin(theta)) on register bit rbit.
-template <typename R>
-__device__ __forceinline__ void reg_rot(C2<R> (&x)[8], int rbit, int pauli, R c, R s)
+// A rotation on register bit rbit of the register sets x...
+template <typename R, int FORM, typename... Xs>
+__device__ __forceinline__ void reg_rot_form(int rbit, int pauli, R m, Xs &...x)
 {
-    if (pauli == 1) reg_rot_p<R, 1>(x, rbit, c, s);
-    else if (pauli == 2) reg_rot_p<R, 2>(x, rbit, c, s);
-    else reg_rot_p<R, 3>(x, rbit, c, s);
+    if (pauli == 1) (reg_rot_p<R, 1, FORM>(x, rbit, m), ...);
+    else if (pauli == 2) (reg_rot_p<R, 2, FORM>(x, rbit, m), ...);
+    else (reg_rot_p<R, 3, FORM>(x, rbit, m), ...);
+}
+
+// dir = -1 gives the adjoint (m has the sign of s in either form).
+template <typename R, typename... Xs>
+__device__ __forceinline__ void reg_rot(int rbit, int pauli, const RotM<R> &r, int dir, Xs &...x)
+{
+    R m = dir > 0 ? r.m : -r.m;
+    asm volatile("" : "+v"(m));
+    if (r.form) reg_rot_form<R, 1>(rbit, pauli, m, x...);
+    else reg_rot_form<R, 0>(rbit, pauli, m, x...);
+}
+
+// A segment's factor on all registers.
+template <typename R>
+__device__ __forceinline__ void reg_scale8(C2<R> (&x)[8], double factor)
+{
+    const R f = (R)factor;
+#pragma unroll
+    for (int u = 0; u < 8; u++) x[u] = mk<R>(f * x[u].x, f * x[u].y);
 }
 
 template <typename R>
@@ -369,6 +425,28 @@ struct RegOffsets {
     }
 };
 
+// Place of tile coordinate c in the LDS buffer of an exchange.  The 64 banks
+// take 32 complex64 amplitudes at once (16 complex128), those of 32 (16) lanes,
+// whose coordinates are the lowest five (four) that the phase does not hold
+// in registers.  With the coordinate itself as the place, a phase that holds
+// low coordinates has its lanes on a few banks: two thirds of the LDS cycles
+// of the first steps were conflicts (0.73 of the forward step's time, 0.43
+// of the backward step's).  So coordinates 5-7 (4-6) are added (GF(2)) onto
+// the bank bits, with the three vectors that leave the fewest conflicts over
+// the phases that ansatz circuits of 10-22 qubits are split into: 1.2 times
+// the cycles of no conflict, 2.4 times without.  The first steps of 192
+// circuits of 10-20 qubits: forward 0.37 -> 0.30 ms, backward 1.47 -> 1.32 ms.
+__host__ __device__ constexpr uint32_t tile_slot(uint32_t c, bool f32)
+{
+    return f32 ? c ^ (0u - ((c >> 5) & 1u) & 27u) ^ (0u - ((c >> 6) & 1u) & 28u) ^ (0u - ((c >> 7) & 1u) & 13u)
+               : c ^ (0u - ((c >> 4) & 1u) & 14u) ^ (0u - ((c >> 5) & 1u) & 13u) ^ (0u - ((c >> 6) & 1u) & 10u);
+}
+
+template <typename R> __device__ __forceinline__ uint32_t tile_slot(uint32_t c)
+{
+    return tile_slot(c, same_type<R, float>::value);
+}
+
 // LDS exchange between the register layouts of phases Q and P: every thread
 // of the block takes part in the barriers; active threads write their
 // registers in Q's layout and read them back in P's.  Returns P's tau.
@@ -376,16 +454,16 @@ template <typename R>
 __device__ __forceinline__ uint32_t bphase_exchange(C2<R> (&x)[8], C2<R> *v, uint32_t tau, const BPhase &Q,
                                                     const BPhase &P, bool active)
 {
-    const uint32_t tn = bphase_tau(threadIdx.x, P);
+    const uint32_t tn = bphase_tau(threadIdx.x, P), so = tile_slot<R>(tau), sn = tile_slot<R>(tn);
     __syncthreads();   // earlier reads of the LDS tile are done
     if (active) {
 #pragma unroll
-        for (int u = 0; u < 8; u++) v[tau | bphase_rho(u, Q)] = x[u];
+        for (int u = 0; u < 8; u++) v[so ^ tile_slot<R>(bphase_rho(u, Q))] = x[u];
     }
     __syncthreads();
     if (active) {
 #pragma unroll
-        for (int u = 0; u < 8; u++) x[u] = v[tn | bphase_rho(u, P)];
+        for (int u = 0; u < 8; u++) x[u] = v[sn ^ tile_slot<R>(bphase_rho(u, P))];
     }
     return tn;
 }
@@ -395,11 +473,11 @@ template <typename R>
 __device__ __forceinline__ uint32_t bphase_exchange2(C2<R> (&x)[8], C2<R> (&y)[8], C2<R> *vphi, C2<R> *vlam,
                                                      uint32_t tau, const BPhase &Q, const BPhase &P, bool active)
 {
-    const uint32_t tn = bphase_tau(threadIdx.x, P);
+    const uint32_t tn = bphase_tau(threadIdx.x, P), so = tile_slot<R>(tau), sn = tile_slot<R>(tn);
     if (active) {
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            const uint32_t c = tau | bphase_rho(u, Q);
+            const uint32_t c = so ^ tile_slot<R>(bphase_rho(u, Q));
             vphi[c] = x[u];
             vlam[c] = y[u];
         }
@@ -408,7 +486,7 @@ __device__ __forceinline__ uint32_t bphase_exchange2(C2<R> (&x)[8], C2<R> (&y)[8
     if (active) {
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            const uint32_t c = tn | bphase_rho(u, P);
+            const uint32_t c = sn ^ tile_slot<R>(bphase_rho(u, P));
             x[u] = vphi[c];
             y[u] = vlam[c];
         }
@@ -416,11 +494,11 @@ __device__ __forceinline__ uint32_t bphase_exchange2(C2<R> (&x)[8], C2<R> (&y)[8
     return tn;
 }
 
-// Operator k (global index; trig holds its cos and sin) of a forward phase.
+// An operator of a forward phase; r: a rotation's table entry.
 // czm carries the sign mask of a run of CZs until the run's last one.
 template <typename R>
-__device__ __forceinline__ void fwd_op(C2<R> (&x)[8], const DOp &op, int k, const double *__restrict__ trig,
-                                       uint32_t tau, uint64_t base, uint32_t &czm)
+__device__ __forceinline__ void fwd_op(C2<R> (&x)[8], const DOp &op, const RotM<R> &r, uint32_t tau, uint64_t base,
+                                       uint32_t &czm)
 {
     if (op.kind == BOP_CZ) {
         czm ^= cz_mask(op, tau, base);
@@ -429,23 +507,23 @@ __device__ __forceinline__ void fwd_op(C2<R> (&x)[8], const DOp &op, int k, cons
             czm = 0;
         }
     } else if (op.kind == BOP_ROT) {
-        reg_rot<R>(x, op.rbit, op.pauli, (R)trig[2 * k], (R)trig[2 * k + 1]);
+        reg_rot<R>(op.rbit, op.pauli, r, +1, x);
     } else {
         C2<R> u[4];
-        op_matrix<R>(op, trig + 2 * k, +1, u);
+        op_matrix<R>(op, nullptr, +1, u);
         reg_gate<R>(x, op.rbit, u);
     }
 }
 
-// Operator k of the adjoint sweep (operators last first): a rotation's
+// An operator of the adjoint sweep (operators last first): a rotation's
 // partial Im <lambda|P|phi> over the thread's register pairs, summed over
 // each row of 16 lanes into red[slot][4 wave + row], then U^dagger on both
 // tiles.  czm as
 // in fwd_op, applied at the run's first CZ (reached last).
 template <typename R>
-__device__ __forceinline__ void bwd_op(C2<R> (&x)[8], C2<R> (&y)[8], const DOp &op, int k,
-                                       const double *__restrict__ trig, uint32_t tau, uint64_t base, uint32_t &czm,
-                                       double (*red)[kRedRows], int lane, int wave)
+__device__ __forceinline__ void bwd_op(C2<R> (&x)[8], C2<R> (&y)[8], const DOp &op, const RotM<R> &r,
+                                       uint32_t tau, uint64_t base, uint32_t &czm, double (*red)[kRedRows], int lane,
+                                       int wave)
 {
     if (op.kind == BOP_CZ) {
         czm ^= cz_mask(op, tau, base);
@@ -467,30 +545,29 @@ __device__ __forceinline__ void bwd_op(C2<R> (&x)[8], C2<R> (&y)[8], const DOp &
         if ((lane & 15) == 15) red[op.slot][4 * wave + (lane >> 4)] = im;
     }
     if (op.kind == BOP_ROT) {
-        const R c = (R)trig[2 * k], sn = -(R)trig[2 * k + 1];   // the adjoint
-        reg_rot<R>(x, op.rbit, op.pauli, c, sn);
-        reg_rot<R>(y, op.rbit, op.pauli, c, sn);
+        reg_rot<R>(op.rbit, op.pauli, r, -1, x, y);
     } else {
         C2<R> u[4];
-        op_matrix<R>(op, trig + 2 * k, -1, u);
+        op_matrix<R>(op, nullptr, -1, u);
         reg_gate<R>(x, op.rbit, u);
         reg_gate<R>(y, op.rbit, u);
     }
 }
 
-// Thread 0.. of the block: the rotation partials of the finished phase
-// [op_begin, op_end) summed over the rows of the wavefronts (fixed order)
-// into gpart, one thread per operator.
-__device__ __forceinline__ void flush_phase(const DOp *__restrict__ ops, int op_begin, int op_end,
-                                            const double (*red)[kRedRows], int nwaves, uint32_t tile,
-                                            double *__restrict__ gpart)
+// The partials of a finished phase's rotations, summed over the rows of the
+// wavefronts (fixed order) into gpart: 32 lanes per rotation, one per row.
+// Needs nothing from memory: the rotations of a phase have consecutive rows.
+__device__ __forceinline__ void flush_phase(const BPhase &P, const DStep &st, const double (*red)[kRedRows],
+                                            int nwaves, uint32_t tile, double *__restrict__ gpart)
 {
-    for (int i = (int)threadIdx.x; i < op_end - op_begin; i += (int)blockDim.x) {
-        const DOp &op = ops[op_begin + i];
-        if (op.grad < 0) continue;
-        double v = 0.0;
-        for (int w = 0; w < 4 * nwaves; w++) v += red[op.slot][w];
-        gpart[op.gpart + tile] = v;
+    const int row = (int)(threadIdx.x & 31u);
+    for (int i = (int)threadIdx.x; (i & ~63) < 32 * P.rots; i += (int)blockDim.x) {
+        const int slot = i >> 5;
+        const bool live = slot < P.rots;
+        double v = live && row < 4 * nwaves ? red[slot][row] : 0.0;
+        v = brow_sum(v);
+        v += __shfl_xor(v, 16, 64);
+        if (live && row == 0) gpart[st.gpart + (uint64_t)(P.rot_begin + slot) * st.tiles + tile] = v;
     }
 }
 
