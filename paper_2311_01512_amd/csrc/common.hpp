@@ -49,8 +49,8 @@ struct qs_qureg {
     int device;
     // scratch owned by the qureg
     double *d_partials;  // per-block partial sums of reductions
-    double *d_result;    // final reduction results
-    double *h_result;    // pinned host copy of d_result
+    double *d_result;    // final reduction results, as the kernels write them
+    double *h_result;    // the same on the host (a qureg's: the same pinned memory)
     unsigned char *d_mat_ring;  // device copies of large gate matrices
     unsigned char *h_mat_ring;  // pinned host staging of the same
     size_t mat_ring_bytes;
@@ -105,7 +105,8 @@ inline unsigned grid_for(uint64_t work, int block, uint64_t max_blocks = 1ull <<
 int stage_matrix(qs_qureg *q, const void *host, size_t bytes, const void **dev);
 
 // Device reduction helpers, defined in reduce.hip.
-int finish_reduction(qs_qureg *q, int blocks, int width, double *out);
+// Sums q->d_partials' `blocks` pairs and waits for the result in out[0..1].
+int finish_reduction(qs_qureg *q, int blocks, double *out);
 // Queue, without waiting: <a|b> of two statevectors on a's stream into
 // out[0..1] (device; a->d_partials as scratch); the fixed-order sums of `rows`
 // rows of `count` doubles into out[0..rows).

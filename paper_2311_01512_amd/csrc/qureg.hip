@@ -188,8 +188,8 @@ int qs_create_qureg(int num_qubits, int is_density, int precision, void *device_
         q->owns_amps = 1;
     }
     if (hipMalloc(&q->d_partials, sizeof(double) * 2 * kReduceBlocks * 4) != hipSuccess ||
-        hipMalloc(&q->d_result, sizeof(double) * kResultSlots) != hipSuccess ||
-        hipHostMalloc(&q->h_result, sizeof(double) * kResultSlots, hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc(&q->h_result, sizeof(double) * kResultSlots, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&q->d_result, q->h_result, 0) != hipSuccess) {
         (void)hipGetLastError();
         return cleanup(QS_E_ALLOC, "scratch allocation failed");
     }
@@ -203,7 +203,6 @@ int qs_destroy_qureg(qs_qureg *q)
     if (q->stream || q->amps) (void)hipStreamSynchronize(q->stream);
     if (q->owns_amps && q->amps) (void)hipFree(q->amps);
     if (q->d_partials) (void)hipFree(q->d_partials);
-    if (q->d_result) (void)hipFree(q->d_result);
     if (q->h_result) (void)hipHostFree(q->h_result);
     if (q->d_mat_ring) (void)hipFree(q->d_mat_ring);
     if (q->h_mat_ring) (void)hipHostFree(q->h_mat_ring);

@@ -4,6 +4,7 @@
 // shuffles, across the block through LDS, and finally across blocks in a
 // fixed order, so a result does not depend on scheduling.
 #include "common.hpp"
+#include "pauli_sum_dev.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -40,8 +41,10 @@ __device__ __forceinline__ void block_sum2(double &re, double &im)
     }
 }
 
-template <typename F>
-__global__ __launch_bounds__(256) void k_reduce(F f, uint64_t n, double *__restrict__ partials)
+// Sums f over [0, n); each block leaves its (re, im) at partials[2 block].
+// THREADS = 1024 for sums that one block takes.
+template <typename F, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_reduce(F f, uint64_t n, double *__restrict__ partials)
 {
     double re = 0.0, im = 0.0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -60,25 +63,46 @@ __global__ __launch_bounds__(256) void k_reduce(F f, uint64_t n, double *__restr
     }
 }
 
-// Fixed-order sum of `blocks` (re, im) partials into result[2*slot..].
-__global__ __launch_bounds__(256) void k_finalize(const double *__restrict__ partials, int blocks,
-                                                   double *__restrict__ result, int slot)
+// Fixed-order sum of `blocks` (re, im) partials into result[0..1]: 1024 threads
+// with four partials in flight each (16384 partials: 26 us with 256 threads
+// and one at a time, 6 us so).
+__global__ __launch_bounds__(1024) void k_finalize(const double2 *__restrict__ partials, int blocks,
+                                                    double *__restrict__ result)
 {
     double re = 0.0, im = 0.0;
-    for (int b = threadIdx.x; b < blocks; b += blockDim.x) {
-        re += partials[2 * b];
-        im += partials[2 * b + 1];
+    const int stride = (int)blockDim.x;
+    int b = (int)threadIdx.x;
+    for (; b + 3 * stride < blocks; b += 4 * stride) {
+        double2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = partials[b + k * stride];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            re += v[k].x;
+            im += v[k].y;
+        }
+    }
+    for (; b < blocks; b += stride) {
+        re += partials[b].x;
+        im += partials[b].y;
     }
     block_sum2(re, im);
     if (threadIdx.x == 0) {
-        result[2 * slot] = re;
-        result[2 * slot + 1] = im;
+        result[0] = re;
+        result[1] = im;
     }
 }
 
 // ---- per-index contributions --------------------------------------------------------
+//
+// kOneBlock: the elements that one block of 1024 threads sums by itself, which
+// leaves the second launch out: 8192 where consecutive elements share lines
+// (4096 amplitudes 13.2 us per call, 15.5 with two launches), fewer where each
+// is a line of its own (a trace of 8192 entries: 10.3 us in one block, 5.5 in
+// two launches) or several.
 
 template <typename R> struct SumSq {
+    static constexpr uint64_t kOneBlock = 8192;
     const C2<R> *a;
     __device__ void operator()(uint64_t i, double &re, double &) const
     {
@@ -89,6 +113,7 @@ template <typename R> struct SumSq {
 
 // Born rule on a statevector: amplitudes whose bit q equals b.
 template <typename R> struct ProbSV {
+    static constexpr uint64_t kOneBlock = 8192;
     const C2<R> *a;
     uint64_t low;    // (1 << q) - 1
     uint64_t bit;    // b << q
@@ -103,6 +128,7 @@ template <typename R> struct ProbSV {
 // Diagonal of a density matrix: rho[k][k] sits at Choi index k (2^N + 1);
 // optionally only k whose bit q equals b.
 template <typename R> struct DiagDM {
+    static constexpr uint64_t kOneBlock = 1024;
     const C2<R> *a;
     uint64_t stride; // 2^N + 1
     uint64_t low, bit;
@@ -117,6 +143,7 @@ template <typename R> struct DiagDM {
 };
 
 template <typename R> struct Inner {
+    static constexpr uint64_t kOneBlock = 8192;
     const C2<R> *a, *b;
     __device__ void operator()(uint64_t i, double &re, double &im) const
     {
@@ -151,6 +178,7 @@ __device__ __forceinline__ void group_coeff(const TermGroup &t, uint64_t x, doub
 // (P psi)_i = beta_j a_j (Eq. "pauli_tensor_amp_update"), beta_x = eta (-1)^{popc(x & yz)}:
 // contribution conj(a_i) c(j) a_j + conj(a_j) c(i) a_i with c(x) = sum_n h_n beta^{(n)}_x.
 template <typename R> struct ExpecPairs {
+    static constexpr uint64_t kOneBlock = 8192;
     const C2<R> *a;
     uint64_t low, xy;
     TermGroup t;
@@ -172,6 +200,7 @@ template <typename R> struct ExpecPairs {
 
 // Diagonal terms (no X or Y): sum_i |a_i|^2 sum_n h_n (-1)^{popc(i & z_n)}.
 template <typename R> struct ExpecDiag {
+    static constexpr uint64_t kOneBlock = 8192;
     const C2<R> *a;
     TermGroup t;
     __device__ void operator()(uint64_t i, double &re, double &im) const
@@ -189,6 +218,8 @@ template <typename R> struct ExpecDiag {
 // P[l][k] is non-zero only for l = k ^ x, where it equals
 // i^{#Y} (-1)^{popc(k & yz)}; so each term gathers the 2^N entries
 // rho[k][k ^ x] = Choi[k + ((k ^ x) << N)] instead of visiting all 4^N.
+constexpr int kDMTermGroup = 4;
+static_assert(kTermsPerLaunch % kDMTermGroup == 0, "whole groups of terms");
 struct DMTerms {
     int count;
     uint64_t x[kTermsPerLaunch], yz[kTermsPerLaunch];
@@ -196,17 +227,32 @@ struct DMTerms {
 };
 
 template <typename R> struct ExpecDM {
+    static constexpr uint64_t kOneBlock = 256;
     const C2<R> *a;
     int N;
     DMTerms t;
-    __device__ void operator()(uint64_t k, double &re, double &im) const
+    // element e: row k of the terms 4 g .. 4 g + 3, e = k + g 2^N, their
+    // gathers in flight together (each lane's is a line of its own; one
+    // thread per row with its terms in turn left most of the chip idle: 20
+    // terms on 13 qubits 16 us, 7 us so)
+    __device__ void operator()(uint64_t e, double &re, double &im) const
     {
-        for (int n = 0; n < t.count; n++) {
-            const C2<R> b = a[k + ((k ^ t.x[n]) << N)];
+        const uint64_t k = e & ((1ULL << N) - 1ULL);
+        const int n0 = kDMTermGroup * (int)(e >> N);
+        C2<R> b[kDMTermGroup];
+#pragma unroll
+        for (int u = 0; u < kDMTermGroup; u++) {
+            const int n = n0 + u < t.count ? n0 + u : n0;
+            b[u] = a[k + ((k ^ t.x[n]) << N)];
+        }
+#pragma unroll
+        for (int u = 0; u < kDMTermGroup; u++) {
+            const int n = n0 + u;
+            if (n >= t.count) break;
             const double s = (__popcll(k & t.yz[n]) & 1) ? -1.0 : 1.0;
             const double c_re = s * t.cre[n], c_im = s * t.cim[n];
-            re += c_re * b.x - c_im * b.y;
-            im += c_re * b.y + c_im * b.x;
+            re += c_re * b[u].x - c_im * b[u].y;
+            im += c_re * b[u].y + c_im * b[u].x;
         }
     }
 };
@@ -225,8 +271,10 @@ template <typename R> struct ExpecDM {
 // imaginary otherwise (partners i, j contribute conjugate products whose signs
 // agree or differ), so a term accumulates one real number: the sum of
 // (-1)^{popc(j & yz_n)} Re or Im of conj(a_i) a_j; the host applies h_n i^{#Y}.
-// Block of 256 threads; thread t holds elements t + 256 u, u < E = 2^(d-8);
-// d <= 11 and L = 4 (runs of 16 contiguous amplitudes), so m = 7 masks per span.
+// Block of 256 threads; thread t holds elements t + 256 u, u < 8; d = 11 and
+// L = 4 (runs of 16 contiguous amplitudes), so m = 7 masks per span.
+constexpr int kTileBits = 11;
+constexpr int kTileRegs = 1 << (kTileBits - 8);
 constexpr int kTileTerms = 8;
 constexpr int kTileBlocks = 4096;   // most blocks of one launch
 
@@ -238,7 +286,7 @@ struct TileTermSet {
     uint32_t zl[kTileTerms];        // coordinate sign mask, thread bits
     uint32_t zh[kTileTerms];        // coordinate sign mask, register bits
     uint64_t yz[kTileTerms];        // sign mask of the term (tile base parity)
-    int pair[kTileTerms];           // half sums (E = 8): register bit 0-2 or 8 + thread bit; -1: full sum
+    int pair[kTileTerms];           // half sums: register bit 0-2 or 8 + thread bit; -1: full sum
 };
 
 struct TileSpan {
@@ -257,10 +305,11 @@ struct TileSpan {
 // Each product Re or Im of conj(own) partner is formed in the precision of
 // the amplitudes (complex64: FP32, whose tile in LDS is then half the bytes);
 // every sum from there on is FP64.
-template <bool IM, int E, typename R>
-__device__ __forceinline__ double term_sum(const unsigned char *__restrict__ tile, const C2<R> (&own)[E], uint32_t tb,
-                                           uint32_t xh, uint32_t zh)
+template <bool IM, typename R>
+__device__ __forceinline__ double term_sum(const unsigned char *__restrict__ tile, const C2<R> (&own)[kTileRegs],
+                                           uint32_t tb, uint32_t xh, uint32_t zh)
 {
+    constexpr int E = kTileRegs;
     double p[E];
 #pragma unroll
     for (int u = 0; u < E; u++) {
@@ -278,7 +327,7 @@ __device__ __forceinline__ double term_sum(const unsigned char *__restrict__ til
     return p[0];
 }
 
-// Half sums (tiles of 8 registers).  For a Hermitian Pauli string the two
+// Half sums.  For a Hermitian Pauli string the two
 // products of a pair (i, j = i ^ x) agree once the term's sign is applied:
 // Re (or Im) of conj(a_i) a_j (-1)^{j.z} equals that of conj(a_j) a_i
 // (-1)^{i.z}, because (-1)^{x.z} is +1 exactly for the terms that sum Re.
@@ -333,33 +382,32 @@ __device__ __forceinline__ double term_half_thr(const unsigned char *__restrict_
 // One term over the thread's elements of the tile with its pairing (pr:
 // TileTermSet::pair); extra: a sign bit the caller adds to the term's
 // parity; twice: the sum counts each pair once.
-template <bool IM, int E, typename R>
-__device__ __forceinline__ double term_any(const unsigned char *__restrict__ tile, const C2<R> (&own)[E], uint32_t t,
+template <bool IM, typename R>
+__device__ __forceinline__ double term_any(const unsigned char *__restrict__ tile, const C2<R> (&own)[kTileRegs], uint32_t t,
                                            uint32_t tp, uint32_t xh, uint32_t zh, int pr, uint32_t &extra,
                                            bool &twice)
 {
     constexpr uint32_t sz = (uint32_t)sizeof(C2<R>);
-    if constexpr (E == 8) {
-        if (pr >= 8) {
-            const uint32_t q = (t >> (pr - 8)) & 1u;
-            extra = q & (zh >> 2);
-            twice = true;
-            return term_half_thr<IM, R>(tile, (t + 1024u * q) * sz, (tp + 1024u * q) * sz, zh);
-        }
-        if (pr >= 0) {
-            twice = true;
-            if (pr == 0) return term_half_reg<IM, 0, R>(tile, own, tp * sz, xh, zh);
-            if (pr == 1) return term_half_reg<IM, 1, R>(tile, own, tp * sz, xh, zh);
-            return term_half_reg<IM, 2, R>(tile, own, tp * sz, xh, zh);
-        }
+    if (pr >= 8) {
+        const uint32_t q = (t >> (pr - 8)) & 1u;
+        extra = q & (zh >> 2);
+        twice = true;
+        return term_half_thr<IM, R>(tile, (t + 1024u * q) * sz, (tp + 1024u * q) * sz, zh);
     }
-    return term_sum<IM, E, R>(tile, own, tp * sz, xh, zh);
+    if (pr >= 0) {
+        twice = true;
+        if (pr == 0) return term_half_reg<IM, 0, R>(tile, own, tp * sz, xh, zh);
+        if (pr == 1) return term_half_reg<IM, 1, R>(tile, own, tp * sz, xh, zh);
+        return term_half_reg<IM, 2, R>(tile, own, tp * sz, xh, zh);
+    }
+    return term_sum<IM, R>(tile, own, tp * sz, xh, zh);
 }
 
-template <typename R, int E>
+template <typename R>
 __global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a, uint64_t num_tiles, TileSpan sp,
                                                      TileTermSet ts, double *__restrict__ partials)
 {
+    constexpr int E = kTileRegs;
     __shared__ C2<R> tile[256 * E];
     __shared__ double red[kTileTerms][4];
     const uint32_t t = threadIdx.x;
@@ -411,8 +459,8 @@ __global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a
                 bool twice = false;
                 const double s =
                     ((ts.kind >> n) & 1)
-                        ? term_any<true, E, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice)
-                        : term_any<false, E, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice);
+                        ? term_any<true, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice)
+                        : term_any<false, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice);
                 const uint32_t par = (uint32_t)__popcll(base & ts.yz[n]) + (uint32_t)__popc(ts.xh[n] & ts.zh[n]) +
                                      (uint32_t)__popc(tp & ts.zl[n]) + extra;
                 const double w = twice ? 2.0 : 1.0;
@@ -434,15 +482,41 @@ __global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a
         partials[(size_t)t * gridDim.x + blockIdx.x] = ((red[t][0] + red[t][1]) + red[t][2]) + red[t][3];
 }
 
-// Term n's block partials summed in block order into result[slot0 + n].
+// Row n's `blocks` partials summed in a fixed order into result[n].
 __global__ __launch_bounds__(256) void k_finalize_terms(const double *__restrict__ partials, int blocks,
-                                                         double *__restrict__ result, int slot0)
+                                                         double *__restrict__ result)
 {
     double re = 0.0, im = 0.0;
     const double *p = partials + (size_t)blockIdx.x * blocks;
     for (int b = threadIdx.x; b < blocks; b += blockDim.x) re += p[b];
     block_sum2(re, im);
-    if (threadIdx.x == 0) result[slot0 + blockIdx.x] = re;
+    if (threadIdx.x == 0) result[blockIdx.x] = re;
+}
+
+// Energy by gathers: the block's partial of sum_i Re conj(psi_i) (H psi)_i over
+// 256 U amplitudes, every term in one launch (add_pauli_terms; products and
+// sums in FP64).
+template <typename R, int U>
+__global__ __launch_bounds__(256) void k_expec_gather(const C2<R> *__restrict__ psi, PauliTerms p,
+                                                       double *__restrict__ partials)
+{
+    const uint64_t first = (uint64_t)blockIdx.x * (256 * U);
+    const uint32_t t = threadIdx.x;
+    double re[U], im[U], e = 0.0, zero = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; u++) re[u] = im[u] = 0.0;
+    add_pauli_terms<R, U, false>(re, im, psi, first, t, p.t, 0, p.real);
+    add_pauli_terms<R, U, true>(re, im, psi, first, t, p.t, p.real, p.count);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const C2<R> v = psi[first + 256u * u + t];
+        e += (double)v.x * re[u] + (double)v.y * im[u];
+    }
+    block_sum2(e, zero);
+    if (t == 0) {
+        partials[2 * blockIdx.x] = e;
+        partials[2 * blockIdx.x + 1] = 0.0;
+    }
 }
 
 // ---- purity: Tr(rho^2) = sum_{k,l} rho[k][l] rho[l][k] ---------------------------------
@@ -594,59 +668,70 @@ __global__ __launch_bounds__(1024) void k_partial_trace(const C2<R> *__restrict_
 
 // ---- host drivers ----------------------------------------------------------------------
 
-template <typename F>
-static int run_reduce(qs_qureg *q, const F &f, uint64_t n, int slot)
+// Queues the fixed-order sum of q->d_partials' `blocks` pairs into result[0..1].
+static int queue_finalize(qs_qureg *q, int blocks, double *result)
 {
-    const int blocks = (int)grid_for(n, 256, kReduceBlocks);
-    hipLaunchKernelGGL(k_reduce<F>, dim3(blocks), dim3(256), 0, q->stream, f, n, q->d_partials);
-    QS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, q->stream, (const double *)q->d_partials, blocks,
-                       q->d_result, slot);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, q->stream, (const double2 *)q->d_partials, blocks, result);
     QS_LAUNCH_CHECK();
     return QS_OK;
 }
 
+// Queues the sum of f over [0, n) into result[0..1] (device-visible).
+template <typename F>
+static int queue_reduce(qs_qureg *q, const F &f, uint64_t n, double *result)
+{
+    if (n <= F::kOneBlock) {
+        hipLaunchKernelGGL((k_reduce<F, 1024>), dim3(1), dim3(1024), 0, q->stream, f, n, result);
+        QS_LAUNCH_CHECK();
+        return QS_OK;
+    }
+    const int blocks = (int)grid_for(n, 256, kReduceBlocks);
+    hipLaunchKernelGGL((k_reduce<F, 256>), dim3(blocks), dim3(256), 0, q->stream, f, n, q->d_partials);
+    QS_LAUNCH_CHECK();
+    return queue_finalize(q, blocks, result);
+}
+
+template <typename F>
+static int run_reduce(qs_qureg *q, const F &f, uint64_t n, int slot)
+{
+    return queue_reduce(q, f, n, q->d_result + 2 * slot);
+}
+
 int queue_inner_product(qs_qureg *a, const qs_qureg *b, double *out)
 {
-    const int blocks = (int)grid_for(a->num_amps, 256, kReduceBlocks);
-    if (a->precision == QS_C64) {
-        const Inner<float> f{(const float2 *)a->amps, (const float2 *)b->amps};
-        hipLaunchKernelGGL(k_reduce<Inner<float>>, dim3(blocks), dim3(256), 0, a->stream, f, a->num_amps, a->d_partials);
-    } else {
-        const Inner<double> f{(const double2 *)a->amps, (const double2 *)b->amps};
-        hipLaunchKernelGGL(k_reduce<Inner<double>>, dim3(blocks), dim3(256), 0, a->stream, f, a->num_amps, a->d_partials);
-    }
-    QS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, a->stream, (const double *)a->d_partials, blocks, out, 0);
-    QS_LAUNCH_CHECK();
-    return QS_OK;
+    return a->precision == QS_C64
+               ? queue_reduce(a, Inner<float>{(const float2 *)a->amps, (const float2 *)b->amps}, a->num_amps, out)
+               : queue_reduce(a, Inner<double>{(const double2 *)a->amps, (const double2 *)b->amps}, a->num_amps, out);
 }
 
 int queue_row_sums(hipStream_t stream, const double *partials, int rows, int count, double *out)
 {
     if (rows < 1) return QS_OK;
-    hipLaunchKernelGGL(k_finalize_terms, dim3(rows), dim3(256), 0, stream, partials, count, out, 0);
+    hipLaunchKernelGGL(k_finalize_terms, dim3(rows), dim3(256), 0, stream, partials, count, out);
     QS_LAUNCH_CHECK();
     return QS_OK;
 }
 
-// Copies result slots [0, nslots) back and waits.
-static int fetch(qs_qureg *q, int nslots)
+// Waits for the result slots' first `count` doubles on the host.  A qureg's
+// slots are pinned host memory that the kernels write (a copy of 16 bytes cost
+// a launch and 4 us of its own); others are copied.
+static int fetch_values(qs_qureg *q, int count)
 {
-    QS_HIP(hipMemcpyAsync(q->h_result, q->d_result, sizeof(double) * 2 * nslots, hipMemcpyDeviceToHost, q->stream));
+    if (q->h_result != q->d_result)
+        QS_HIP(hipMemcpyAsync(q->h_result, q->d_result, sizeof(double) * count, hipMemcpyDeviceToHost, q->stream));
     QS_HIP(hipStreamSynchronize(q->stream));
     return QS_OK;
 }
 
-int finish_reduction(qs_qureg *q, int blocks, int slot, double *out)
+static int fetch(qs_qureg *q, int nslots) { return fetch_values(q, 2 * nslots); }
+
+int finish_reduction(qs_qureg *q, int blocks, double *out)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, q->stream, (const double *)q->d_partials, blocks,
-                       q->d_result, slot);
-    QS_LAUNCH_CHECK();
-    int rc = fetch(q, slot + 1);
+    int rc = queue_finalize(q, blocks, q->d_result);
+    if (rc == QS_OK) rc = fetch(q, 1);
     if (rc != QS_OK) return rc;
-    out[0] = q->h_result[2 * slot];
-    out[1] = q->h_result[2 * slot + 1];
+    out[0] = q->h_result[0];
+    out[1] = q->h_result[1];
     return QS_OK;
 }
 
@@ -757,52 +842,37 @@ static int expec_sv(qs_qureg *q, const int *codes, const double *coeffs, int T, 
     return QS_OK;
 }
 
-// Blocks of one k_expec_tiles<R, E> launch: twice as many as stay resident
+// Blocks of one k_expec_tiles<R> launch: twice as many as stay resident
 // (at most kTileBlocks), each walking tiles by a fixed stride.  On the
 // 20-term sum over 28 qubits, against 1024 blocks: complex64 1.60 against
 // 1.76 ms per call (as many as stay resident: 1.65 ms), complex128 2.41
 // against 2.66 ms; runs of consecutive tiles per block were no faster.
 template <typename R>
-static int expec_tile_blocks(int E, int device)
+static int expec_tile_blocks(int device)
 {
     static std::mutex mu;
-    static std::map<std::pair<int, int>, int> cache;
+    static std::map<int, int> cache;
     std::lock_guard<std::mutex> lock(mu);
-    const auto key = std::make_pair(device, E);
-    auto it = cache.find(key);
+    auto it = cache.find(device);
     if (it != cache.end()) return it->second;
     int per_cu = 0, cus = 0;
-    hipError_t e1;
-    if (E == 1) e1 = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_expec_tiles<R, 1>, 256, 0);
-    else if (E == 2) e1 = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_expec_tiles<R, 2>, 256, 0);
-    else if (E == 4) e1 = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_expec_tiles<R, 4>, 256, 0);
-    else e1 = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_expec_tiles<R, 8>, 256, 0);
+    const hipError_t e1 = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_expec_tiles<R>, 256, 0);
     const hipError_t e2 = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     int blocks = 1024;
     if (e1 == hipSuccess && e2 == hipSuccess && per_cu >= 1 && cus >= 1) blocks = std::min(kTileBlocks, 2 * per_cu * cus);
     else (void)hipGetLastError();
-    cache.emplace(key, blocks);
+    cache.emplace(device, blocks);
     return blocks;
 }
 
-template <typename R>
-static void launch_expec_tiles(int E, int blocks, hipStream_t st, const C2<R> *amps, uint64_t num_tiles,
-                               const TileSpan &sp, const TileTermSet &ts, double *partials)
-{
-    if (E == 1) hipLaunchKernelGGL((k_expec_tiles<R, 1>), dim3(blocks), dim3(256), 0, st, amps, num_tiles, sp, ts, partials);
-    else if (E == 2) hipLaunchKernelGGL((k_expec_tiles<R, 2>), dim3(blocks), dim3(256), 0, st, amps, num_tiles, sp, ts, partials);
-    else if (E == 4) hipLaunchKernelGGL((k_expec_tiles<R, 4>), dim3(blocks), dim3(256), 0, st, amps, num_tiles, sp, ts, partials);
-    else hipLaunchKernelGGL((k_expec_tiles<R, 8>), dim3(blocks), dim3(256), 0, st, amps, num_tiles, sp, ts, partials);
-}
-
-// Tiled Pauli sum for N >= 8: spans of L low qubits plus up to d - L flip
+// Tiled Pauli sum for N >= 11: spans of L low qubits plus up to d - L flip
 // masks (greedy, first fit over the distinct masks in ascending order), each
 // span's terms in launches of up to kTileTerms.
 template <typename R>
 static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, int T, double *re, double *im)
 {
     const int N = q->num_qubits;
-    const int d = std::min(N, 11);
+    const int d = kTileBits;
     const int L = 4;
     const int m = d - L;
     const uint64_t lowmask = (1ULL << L) - 1ULL;
@@ -833,8 +903,8 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
     std::vector<int> slot_term;
     auto flush = [&]() -> int {
         if (slot == 0) return QS_OK;
-        QS_HIP(hipMemcpyAsync(q->h_result, q->d_result, sizeof(double) * slot, hipMemcpyDeviceToHost, q->stream));
-        QS_HIP(hipStreamSynchronize(q->stream));
+        const int rc = fetch_values(q, slot);
+        if (rc != QS_OK) return rc;
         for (int s = 0; s < slot; s++) {
             const int t = slot_term[s];
             const double v = q->h_result[s];
@@ -895,8 +965,7 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
         sp.plan.n = d;
         for (int k = 0; k < d; k++) sp.plan.low[k] = (1ULL << pos[k]) - 1ULL;
         for (int k = 0; k < 8; k++) sp.coord[k] = coord[k];
-        const int E = 1 << (d - 8);
-        for (int u = 0; u < E; u++) {
+        for (int u = 0; u < kTileRegs; u++) {
             uint64_t o = 0;
             for (int k = 0; k < d - 8; k++)
                 if ((u >> k) & 1) o ^= coord[8 + k];
@@ -919,7 +988,7 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
         for (uint64_t x : chosen)
             for (int t : by_mask[x]) terms.push_back(t);
         const uint64_t num_tiles = 1ULL << (N - d);
-        const int blocks = (int)std::min<uint64_t>(num_tiles, (uint64_t)expec_tile_blocks<R>(E, q->device));
+        const int blocks = (int)std::min<uint64_t>(num_tiles, (uint64_t)expec_tile_blocks<R>(q->device));
         for (size_t b0 = 0; b0 < terms.size(); b0 += kTileTerms) {
             TileTermSet ts{};
             ts.count = (int)std::min<size_t>(kTileTerms, terms.size() - b0);
@@ -936,18 +1005,19 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
                 ts.zh[n] = zc >> 8;
                 ts.yz[n] = yzs[t];
                 // pairing of the half sums: the lowest flipped register bit,
-                // else the highest flipped thread bit (tiles of 8 registers)
+                // else the highest flipped thread bit
                 ts.pair[n] = -1;
-                if (E == 8 && ts.xh[n]) ts.pair[n] = __builtin_ctz(ts.xh[n]);
-                else if (E == 8 && ts.xl[n]) ts.pair[n] = 8 + (31 - __builtin_clz(ts.xl[n]));
+                if (ts.xh[n]) ts.pair[n] = __builtin_ctz(ts.xh[n]);
+                else if (ts.xl[n]) ts.pair[n] = 8 + (31 - __builtin_clz(ts.xl[n]));
                 if (__builtin_popcountll(xs[t] & yzs[t]) & 1) ts.kind |= 1u << n;
                 slot_term.push_back(t);
             }
-            launch_expec_tiles<R>(E, blocks, q->stream, (const C2<R> *)q->amps, num_tiles, sp, ts, q->d_partials);
+            // one block's sums are the terms' values already
+            hipLaunchKernelGGL((k_expec_tiles<R>), dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps,
+                               num_tiles, sp, ts, q->d_partials);
             QS_LAUNCH_CHECK();
-            hipLaunchKernelGGL(k_finalize_terms, dim3(ts.count), dim3(256), 0, q->stream,
-                               (const double *)q->d_partials, blocks, q->d_result, slot);
-            QS_LAUNCH_CHECK();
+            const int rc = queue_row_sums(q->stream, q->d_partials, ts.count, blocks, q->d_result + slot);
+            if (rc != QS_OK) return rc;
             slot += ts.count;
         }
     }
@@ -955,6 +1025,49 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
     if (rc != QS_OK) return rc;
     *re = acc_re;
     *im = acc_im;
+    return QS_OK;
+}
+
+// Largest state whose Pauli sum is formed by gathers, which cost one or two
+// launches for all terms, but read the state once per term from the caches;
+// tiles cost two launches per span of 7 masks.  Per call with 20 / 60 terms,
+// gathers against tiles: 12 qubits complex128 24 / 33 against 56 / 114 us;
+// 8 MiB, 20 qubits complex64 38 / 60 against 51 / 123 us; 16 MiB, 20 qubits
+// complex128 58 / 123 against 55 / 136 us, 22 qubits complex64 108 / 263
+// against 83 / 215 us.
+constexpr uint64_t kGatherBytes = 8u << 20;
+
+// The Pauli sum by gathers, for N >= 8: one launch for up to kSumTerms terms.
+template <typename R>
+static int expec_sv_gather(qs_qureg *q, const int *codes, const double *coeffs, int T, double *re)
+{
+    const int N = q->num_qubits;
+    for (size_t i = 0; i < (size_t)T * N; i++)
+        if (codes[i] < 0 || codes[i] > 3) return fail(QS_E_ARG, "Pauli codes are 0..3");
+    const int U = N >= 10 ? 4 : 1;
+    const int blocks = (int)(q->num_amps / (256 * U));
+    double sum = 0.0;
+    int slot = 0;
+    for (int b = 0; b < T; b += kSumTerms) {
+        const PauliTerms p = pauli_terms(codes, coeffs, N, b, std::min(b + kSumTerms, T));
+        double *result = q->d_result + 2 * slot, *partials = blocks == 1 ? result : q->d_partials;
+        if (U == 4)
+            hipLaunchKernelGGL((k_expec_gather<R, 4>), dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, p,
+                               partials);
+        else
+            hipLaunchKernelGGL((k_expec_gather<R, 1>), dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, p,
+                               partials);
+        QS_LAUNCH_CHECK();
+        int rc = blocks == 1 ? QS_OK : queue_finalize(q, blocks, result);
+        if (rc == QS_OK && (++slot == kResultSlots / 2 || b + kSumTerms >= T)) {
+            rc = fetch(q, slot);
+            if (rc == QS_OK)
+                for (int s = 0; s < slot; s++) sum += q->h_result[2 * s];
+            slot = 0;
+        }
+        if (rc != QS_OK) return rc;
+    }
+    *re = sum;
     return QS_OK;
 }
 
@@ -983,7 +1096,8 @@ static int expec_dm(qs_qureg *q, const int *codes, const double *coeffs, int T, 
             g.cre[n] = c.real();
             g.cim[n] = c.imag();
         }
-        int rc = run_reduce(q, ExpecDM<R>{(const C2<R> *)q->amps, N, g}, 1ULL << N, 0);
+        int rc = run_reduce(q, ExpecDM<R>{(const C2<R> *)q->amps, N, g},
+                            (uint64_t)((g.count + kDMTermGroup - 1) / kDMTermGroup) << N, 0);
         if (rc == QS_OK) rc = fetch(q, 1);
         if (rc != QS_OK) return rc;
         acc_re += q->h_result[0];
@@ -1004,13 +1118,13 @@ static int purity(qs_qureg *q, double *re, double *im)
     const uint64_t pairs = T * (T + 1) / 2;
     const int blocks = (int)std::min<uint64_t>(pairs, kReduceBlocks);
     hipLaunchKernelGGL(k_purity<R>, dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, N, TS, T, pairs,
-                       q->d_partials);
+                       blocks == 1 ? q->d_result : q->d_partials);
     QS_LAUNCH_CHECK();
-    double out[2];
-    int rc = finish_reduction(q, blocks, 0, out);
+    int rc = blocks == 1 ? QS_OK : queue_finalize(q, blocks, q->d_result);
+    if (rc == QS_OK) rc = fetch(q, 1);
     if (rc != QS_OK) return rc;
-    *re = out[0];
-    if (im) *im = out[1];
+    *re = q->h_result[0];
+    if (im) *im = q->h_result[1];
     return QS_OK;
 }
 
@@ -1053,8 +1167,8 @@ static int partial_trace(const qs_qureg *in, const std::vector<int> &t, qs_qureg
     return QS_OK;
 }
 
-// Pauli sum on a statevector (tiles for N >= 8, else pairs per flip mask)
-// or a density matrix.  Scratch: q->d_partials (at most kExpecPartials
+// Pauli sum on a statevector (by gathers or by tiles for N >= 8, else pairs per
+// flip mask) or a density matrix.  Scratch: q->d_partials (at most kExpecPartials
 // doubles: 2 per reduction block, or one per tile block and term) and
 // q->d_result (kResultSlots doubles); no staging of matrices.
 static_assert(kExpecPartials >= 2 * (size_t)kReduceBlocks, "reduction partials exceed the bound");
@@ -1065,10 +1179,14 @@ int expec_pauli_sum(qs_qureg *q, const int *paulis, const double *coeffs, int nu
     if (num_terms < 0 || (num_terms > 0 && (!paulis || !coeffs))) return fail(QS_E_ARG, "bad Pauli sum");
     double re = 0.0, im = 0.0;
     int rc = QS_OK;
+    const uint64_t amp_bytes = q->precision == QS_C64 ? sizeof(float2) : sizeof(double2);
     if (num_terms > 0) {
         if (q->is_density)
             rc = q->precision == QS_C64 ? expec_dm<float>(q, paulis, coeffs, num_terms, &re, &im)
                                         : expec_dm<double>(q, paulis, coeffs, num_terms, &re, &im);
+        else if (q->num_qubits >= 8 && q->num_amps * amp_bytes <= kGatherBytes)
+            rc = q->precision == QS_C64 ? expec_sv_gather<float>(q, paulis, coeffs, num_terms, &re)
+                                        : expec_sv_gather<double>(q, paulis, coeffs, num_terms, &re);
         else if (q->num_qubits >= 8)
             rc = q->precision == QS_C64 ? expec_sv_tiles<float>(q, paulis, coeffs, num_terms, &re, &im)
                                         : expec_sv_tiles<double>(q, paulis, coeffs, num_terms, &re, &im);
@@ -1142,9 +1260,7 @@ int qs_calc_inner_product(const qs_qureg *ca, const qs_qureg *cb, double *out_re
     if (a->num_qubits != b->num_qubits) return fail(QS_E_ARG, "qubit counts differ");
     if (a->precision != b->precision) return fail(QS_E_TYPE, "precisions differ");
     if (a->stream != b->stream) QS_HIP(hipStreamSynchronize(b->stream));
-    int rc = a->precision == QS_C64
-                 ? run_reduce(a, Inner<float>{(const float2 *)a->amps, (const float2 *)b->amps}, a->num_amps, 0)
-                 : run_reduce(a, Inner<double>{(const double2 *)a->amps, (const double2 *)b->amps}, a->num_amps, 0);
+    int rc = queue_inner_product(a, b, a->d_result);
     if (rc == QS_OK) rc = fetch(a, 1);
     if (rc != QS_OK) return rc;
     if (out_re) *out_re = a->h_result[0];
