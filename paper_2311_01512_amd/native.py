@@ -4,6 +4,7 @@ has not been built; there is no fallback implementation.
 """
 import ctypes as C
 import os
+from array import array
 
 import numpy as np
 
@@ -132,6 +133,33 @@ def ptr(a):
     return None if a is None else a.ctypes.data_as(C.c_void_p)
 
 
+# Arguments of the calls that act on a state, where marshalling is most of a
+# small state's time (a gate on 12 qubits: MARSH us per call).  Each
+# returns the object that holds the values, their address, and for lists
+# their number; the caller keeps the object for the call.
+
+def _int_list(xs):
+    """A list of C ints (OverflowError outside their range)."""
+    if type(xs) is not tuple and type(xs) is not list:
+        xs = list(xs)
+    try:
+        a = array("i", xs)
+    except TypeError:   # numbers that are no integers, as NumPy converts them
+        a = ints(xs)
+        return a, a.ctypes.data, a.size
+    return a, a.buffer_info()[0], len(a)
+
+
+def _matrix(m):
+    """A matrix as contiguous interleaved (re, im) doubles."""
+    m = np.asarray(m, dtype=np.complex128)
+    if m.nbytes <= 4096:   # a copy costs less than asking NumPy for the address
+        b = m.tobytes()
+        return m, b
+    m = np.ascontiguousarray(m)
+    return m, m.ctypes.data
+
+
 def cmatrix(m):
     """Complex matrix -> contiguous interleaved (re, im) float64 array."""
     m = np.ascontiguousarray(np.asarray(m, dtype=np.complex128))
@@ -196,18 +224,17 @@ def _square(m, dim, what):
 
 
 def qs_apply_multi_ctrl_multi_targ_unitary(q, ctrls, targs, matrix):
-    c, t = ints(ctrls), ints(targs)
-    _square(matrix, 1 << t.size, "matrix")
-    m = cmatrix(matrix)
-    check(lib.qs_apply_multi_ctrl_multi_targ_unitary(q, ptr(c), c.size, ptr(t), t.size, ptr(m)),
-          "qs_apply_multi_ctrl_multi_targ_unitary")
+    (c, cp, nc), (t, tp, nt) = _int_list(ctrls), _int_list(targs)
+    _square(matrix, 1 << nt, "matrix")
+    m, mp = _matrix(matrix)
+    check(lib.qs_apply_multi_ctrl_multi_targ_unitary(q, cp, nc, tp, nt, mp), "qs_apply_multi_ctrl_multi_targ_unitary")
 
 
 def qs_apply_pauli_gadget(q, targs, paulis, theta):
-    t, p = ints(targs), ints(paulis)
-    if t.size != p.size:
+    (t, tp, n), (p, pp, k) = _int_list(targs), _int_list(paulis)
+    if n != k:
         raise ValueError("targs and paulis differ in length")
-    check(lib.qs_apply_pauli_gadget(q, ptr(t), ptr(p), t.size, float(theta)), "qs_apply_pauli_gadget")
+    check(lib.qs_apply_pauli_gadget(q, tp, pp, n, float(theta)), "qs_apply_pauli_gadget")
 
 
 def qs_apply_swap(q, qubit1, qubit2):
@@ -215,37 +242,37 @@ def qs_apply_swap(q, qubit1, qubit2):
 
 
 def qs_apply_multi_swap(q, qubits1, qubits2):
-    a, b = ints(qubits1), ints(qubits2)
-    if a.size != b.size:
+    (a, ap, n), (b, bp, k) = _int_list(qubits1), _int_list(qubits2)
+    if n != k:
         raise ValueError("qubits1 and qubits2 differ in length")
-    check(lib.qs_apply_multi_swap(q, ptr(a), ptr(b), a.size), "qs_apply_multi_swap")
+    check(lib.qs_apply_multi_swap(q, ap, bp, n), "qs_apply_multi_swap")
 
 
 def qs_apply_pauli_tensor(q, targs, paulis):
-    t, p = ints(targs), ints(paulis)
-    if t.size != p.size:
+    (t, tp, n), (p, pp, k) = _int_list(targs), _int_list(paulis)
+    if n != k:
         raise ValueError("targs and paulis differ in length")
-    check(lib.qs_apply_pauli_tensor(q, ptr(t), ptr(p), t.size), "qs_apply_pauli_tensor")
+    check(lib.qs_apply_pauli_tensor(q, tp, pp, n), "qs_apply_pauli_tensor")
 
 
 def qs_apply_phase_gadget(q, targs, theta):
-    t = ints(targs)
-    check(lib.qs_apply_phase_gadget(q, ptr(t), t.size, float(theta)), "qs_apply_phase_gadget")
+    t, tp, n = _int_list(targs)
+    check(lib.qs_apply_phase_gadget(q, tp, n, float(theta)), "qs_apply_phase_gadget")
 
 
 def qs_apply_superop(q, targs, superop):
-    t = ints(targs)
-    _square(superop, 1 << (2 * t.size), "superoperator")
-    s = cmatrix(superop)
-    check(lib.qs_apply_superop(q, ptr(t), t.size, ptr(s)), "qs_apply_superop")
+    t, tp, n = _int_list(targs)
+    _square(superop, 1 << (2 * n), "superoperator")
+    s, sp = _matrix(superop)
+    check(lib.qs_apply_superop(q, tp, n, sp), "qs_apply_superop")
 
 
 def qs_apply_kraus_map(q, targs, kraus):
-    t = ints(targs)
-    k = np.ascontiguousarray(np.asarray(kraus, dtype=np.complex128))
-    if k.ndim != 3 or k.shape[1:] != (1 << t.size, 1 << t.size):
-        raise ValueError(f"Kraus operators must have shape (M, {1 << t.size}, {1 << t.size})")
-    check(lib.qs_apply_kraus_map(q, ptr(t), t.size, ptr(k.view(np.float64)), k.shape[0]), "qs_apply_kraus_map")
+    t, tp, n = _int_list(targs)
+    k, kp = _matrix(kraus)
+    if k.ndim != 3 or k.shape[1:] != (1 << n, 1 << n):
+        raise ValueError(f"Kraus operators must have shape (M, {1 << n}, {1 << n})")
+    check(lib.qs_apply_kraus_map(q, tp, n, kp, k.shape[0]), "qs_apply_kraus_map")
 
 
 def qs_apply_dephasing(q, target, p):
@@ -270,8 +297,8 @@ def qs_apply_damping(q, target, p):
 
 
 def qs_calc_partial_trace(q_in, targs, q_out):
-    t = ints(targs)
-    check(lib.qs_calc_partial_trace(q_in, ptr(t), t.size, q_out), "qs_calc_partial_trace")
+    t, tp, n = _int_list(targs)
+    check(lib.qs_calc_partial_trace(q_in, tp, n, q_out), "qs_calc_partial_trace")
 
 
 def qs_get_info(q):
