@@ -23,7 +23,7 @@
  *    failure nothing is modified and qs_last_error() describes the problem.
  *    No exception crosses this boundary.
  *  - Calls that update a state are asynchronous on the qureg's HIP stream.
- *    Calls that return a scalar synchronise that stream before returning.
+ *    Calls that return a scalar wait for that stream's work before returning.
  *  - Host arrays passed in are read during the call only; the caller keeps
  *    ownership.  Calls on one qureg must not run concurrently from several
  *    host threads.

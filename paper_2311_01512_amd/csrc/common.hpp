@@ -51,6 +51,13 @@ struct qs_qureg {
     double *d_partials;  // per-block partial sums of reductions
     double *d_result;    // final reduction results, as the kernels write them
     double *h_result;    // the same on the host (a qureg's: the same pinned memory)
+    // a counter after the results, which the last kernel of a reduction sets
+    // to `ticket` once its result is written (null: none); signalled: the
+    // kernel queued last does so
+    uint64_t *d_done;
+    volatile uint64_t *h_done;
+    uint64_t ticket;
+    bool signalled;
     unsigned char *d_mat_ring;  // device copies of large gate matrices
     unsigned char *h_mat_ring;  // pinned host staging of the same
     size_t mat_ring_bytes;

@@ -188,11 +188,14 @@ int qs_create_qureg(int num_qubits, int is_density, int precision, void *device_
         q->owns_amps = 1;
     }
     if (hipMalloc(&q->d_partials, sizeof(double) * 2 * kReduceBlocks * 4) != hipSuccess ||
-        hipHostMalloc(&q->h_result, sizeof(double) * kResultSlots, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+        hipHostMalloc(&q->h_result, sizeof(double) * (kResultSlots + 1), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostGetDevicePointer((void **)&q->d_result, q->h_result, 0) != hipSuccess) {
         (void)hipGetLastError();
         return cleanup(QS_E_ALLOC, "scratch allocation failed");
     }
+    q->d_done = (uint64_t *)(q->d_result + kResultSlots);
+    q->h_done = (volatile uint64_t *)(q->h_result + kResultSlots);
+    *q->h_done = 0;
     *out = q;
     return QS_OK;
 }

