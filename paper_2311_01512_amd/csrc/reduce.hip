@@ -289,6 +289,15 @@ template <typename R> struct ExpecDM {
 // (-1)^{popc(j & yz_n)} Re or Im of conj(a_i) a_j; the host applies h_n i^{#Y}.
 // Block of 256 threads; thread t holds elements t + 256 u, u < 8; d = 11 and
 // L = 4 (runs of 16 contiguous amplitudes), so m = 7 masks per span.
+// Scalar instructions outnumbered the vector ones here, a quarter of them the
+// spreading of tile numbers and most others scalar registers spilled to lanes
+// (six fields per term did not fit beside the offsets).  With the fields packed, bases
+// that follow by one addition, a thread's sign bits formed once and, in
+// complex64, one barrier per tile, 28 qubits with 20 terms went from 1513 to
+// 1265 us (27 qubits complex128 1295 -> 1153; two LDS buffers there would
+// halve the blocks in flight).  A launch reads its 2 GiB in 0.42 ms, a plain
+// sum in 0.34.  No gain: five waves per SIMD instead of four, a CU's blocks
+// on neighbouring tiles.
 constexpr int kTileBits = 11;
 constexpr int kTileRegs = 1 << (kTileBits - 8);
 constexpr int kTileTerms = 8;
@@ -296,17 +305,19 @@ constexpr int kTileBlocks = 4096;   // most blocks of one launch
 
 struct TileTermSet {
     int count;
-    uint32_t kind;                  // bit n: term n sums Im (else Re)
-    uint32_t xl[kTileTerms];        // coordinate flip, thread bits (c & 255)
-    uint32_t xh[kTileTerms];        // coordinate flip, register bits (c >> 8)
+    // term n, packed (one scalar register per term through the loop): bits
+    // 0-7 and 8-10 the thread and register bits of its coordinate flip, 11-13
+    // the register bits of its sign mask, 14-18 its half sums' pairing + 1
+    // (register bit 0-2, 8 + thread bit; 0: full sum), 19: sums Im (else Re)
+    uint32_t loop[kTileTerms];
     uint32_t zl[kTileTerms];        // coordinate sign mask, thread bits
-    uint32_t zh[kTileTerms];        // coordinate sign mask, register bits
     uint64_t yz[kTileTerms];        // sign mask of the term (tile base parity)
-    int pair[kTileTerms];           // half sums: register bit 0-2 or 8 + thread bit; -1: full sum
 };
 
 struct TileSpan {
     InsertPlan plan;                // coset bases: zeros at the d pivot positions
+    uint64_t pivots;                // these positions
+    uint64_t step;                  // the grid's size, spread as tile numbers are
     uint64_t coord[8];              // offsets of coordinates 0..7 (thread bits)
     uint64_t offu[8];               // offset of element 256 u
 };
@@ -396,22 +407,18 @@ __device__ __forceinline__ double term_half_thr(const unsigned char *__restrict_
 }
 
 // One term over the thread's elements of the tile with its pairing (pr:
-// TileTermSet::pair); extra: a sign bit the caller adds to the term's
-// parity; twice: the sum counts each pair once.
+// see TileTermSet::loop): the products of half the pairs, or of all; t, tp: the
+// thread's element and its partner.
 template <bool IM, typename R>
 __device__ __forceinline__ double term_any(const unsigned char *__restrict__ tile, const C2<R> (&own)[kTileRegs], uint32_t t,
-                                           uint32_t tp, uint32_t xh, uint32_t zh, int pr, uint32_t &extra,
-                                           bool &twice)
+                                           uint32_t tp, uint32_t xh, uint32_t zh, int pr)
 {
     constexpr uint32_t sz = (uint32_t)sizeof(C2<R>);
     if (pr >= 8) {
         const uint32_t q = (t >> (pr - 8)) & 1u;
-        extra = q & (zh >> 2);
-        twice = true;
         return term_half_thr<IM, R>(tile, (t + 1024u * q) * sz, (tp + 1024u * q) * sz, zh);
     }
     if (pr >= 0) {
-        twice = true;
         if (pr == 0) return term_half_reg<IM, 0, R>(tile, own, tp * sz, xh, zh);
         if (pr == 1) return term_half_reg<IM, 1, R>(tile, own, tp * sz, xh, zh);
         return term_half_reg<IM, 2, R>(tile, own, tp * sz, xh, zh);
@@ -420,11 +427,12 @@ __device__ __forceinline__ double term_any(const unsigned char *__restrict__ til
 }
 
 template <typename R>
-__global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a, uint64_t num_tiles, TileSpan sp,
+__global__ __launch_bounds__(256, 4) void k_expec_tiles(const C2<R> *__restrict__ a, uint64_t num_tiles, TileSpan sp,
                                                      TileTermSet ts, double *__restrict__ partials)
 {
     constexpr int E = kTileRegs;
-    __shared__ C2<R> tile[256 * E];
+    constexpr int kBuffers = sizeof(R) == 4 ? 2 : 1;
+    __shared__ C2<R> tile[kBuffers * 256 * E];
     __shared__ double red[kTileTerms][4];
     const uint32_t t = threadIdx.x;
     uint64_t toff = 0;
@@ -432,57 +440,64 @@ __global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a
     for (int k = 0; k < 8; k++)
         if ((t >> k) & 1) toff ^= sp.coord[k];
     double acc[kTileTerms];
+    uint32_t signs = 0;     // bit n: the thread's sign of term n, the tile's aside
 #pragma unroll
-    for (int n = 0; n < kTileTerms; n++) acc[n] = 0.0;
+    for (int n = 0; n < kTileTerms; n++) {
+        acc[n] = 0.0;
+        if (n < ts.count) {
+            const uint32_t w = ts.loop[n], xh = (w >> 8) & 7u, zh = (w >> 11) & 7u, pr1 = (w >> 14) & 31u;
+            uint32_t par = (uint32_t)__popc(xh & zh) + (uint32_t)__popc((t ^ (w & 255u)) & ts.zl[n]);
+            if (pr1 > 8) par += (t >> (pr1 - 9)) & (zh >> 2);
+            signs |= (par & 1u) << n;
+        }
+    }
 
-    uint64_t g = blockIdx.x;
+    // Bases follow each other by an addition whose carries pass over the
+    // pivots.
+    uint64_t g = blockIdx.x, base = insert_zeros(g, sp.plan);
     C2<R> x[E];
     if (g < num_tiles) {
-        const uint64_t b0 = insert_zeros(g, sp.plan);
 #pragma unroll
-        for (int u = 0; u < E; u++) x[u] = a[b0 ^ sp.offu[u] ^ toff];
+        for (int u = 0; u < E; u++) x[u] = a[base ^ sp.offu[u] ^ toff];
     }
+    uint32_t tv = t;        // the thread's element, in the buffer in use
     for (; g < num_tiles; g += gridDim.x) {
-        const uint64_t base = insert_zeros(g, sp.plan);
         C2<R> own[E];
 #pragma unroll
         for (int u = 0; u < E; u++) own[u] = x[u];
-        __syncthreads();    // the previous tile's reads are done
+        // Two buffers in turn: a wave writes this one again only past the
+        // next tile's barrier, which every wave reaches after its reads here.
+        if (kBuffers == 1) __syncthreads();
 #pragma unroll
-        for (int u = 0; u < E; u++) tile[t + 256 * u] = own[u];
+        for (int u = 0; u < E; u++) tile[tv + 256 * u] = own[u];
         __syncthreads();
+        const uint64_t next = ((base | sp.pivots) + sp.step) & ~sp.pivots;
         // the next tile's loads go out before the sums
-        const uint64_t next = g + gridDim.x;
 #pragma unroll
         for (int u = 0; u < E; u++) x[u] = mk<R>(R(0), R(0));
-        if (next < num_tiles) {
-            const uint64_t nb = insert_zeros(next, sp.plan);
+        if (g + gridDim.x < num_tiles) {
 #pragma unroll
-            for (int u = 0; u < E; u++) x[u] = a[nb ^ sp.offu[u] ^ toff];
+            for (int u = 0; u < E; u++) x[u] = a[next ^ sp.offu[u] ^ toff];
         }
-        // t made opaque per tile: the partner addresses of every (term, u)
+        // tv made opaque per tile: the partner addresses of every (term, u)
         // are loop invariants that would otherwise stay live in registers
-        uint32_t tv = t;
         asm volatile("" : "+v"(tv));
 #pragma unroll
         for (int n = 0; n < kTileTerms; n++) {
             if (n < ts.count) {
-                const uint32_t tp = tv ^ ts.xl[n];
-                uint32_t zh = ts.zh[n];      // likewise for the fold signs
-                asm volatile("" : "+s"(zh));
+                uint32_t w = ts.loop[n];     // likewise for the fold signs
+                asm volatile("" : "+s"(w));
+                const uint32_t tp = tv ^ (w & 255u), xh = (w >> 8) & 7u, zh = (w >> 11) & 7u;
+                const int pr = (int)((w >> 14) & 31u) - 1;
                 const unsigned char *tl = reinterpret_cast<const unsigned char *>(tile);
-                uint32_t extra = 0;
-                bool twice = false;
-                const double s =
-                    ((ts.kind >> n) & 1)
-                        ? term_any<true, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice)
-                        : term_any<false, R>(tl, own, tv, tp, ts.xh[n], zh, ts.pair[n], extra, twice);
-                const uint32_t par = (uint32_t)__popcll(base & ts.yz[n]) + (uint32_t)__popc(ts.xh[n] & ts.zh[n]) +
-                                     (uint32_t)__popc(tp & ts.zl[n]) + extra;
-                const double w = twice ? 2.0 : 1.0;
-                acc[n] = fma((par & 1) ? -w : w, s, acc[n]);
+                const double s = (w >> 19) ? term_any<true, R>(tl, own, tv, tp, xh, zh, pr)
+                                           : term_any<false, R>(tl, own, tv, tp, xh, zh, pr);
+                const uint32_t flip = (signs ^ ((uint32_t)__popcll(base & ts.yz[n]) << n)) << (31 - n);
+                acc[n] += __hiloint2double(__double2hiint(s) ^ (int)(flip & 0x80000000u), __double2loint(s));
             }
         }
+        base = next;
+        if (kBuffers == 2) tv ^= 256 * E;
     }
     // per term: wave sums, then the four waves in order
     const int lane = t & 63, wave = t >> 6;
@@ -490,7 +505,8 @@ __global__ __launch_bounds__(256) void k_expec_tiles(const C2<R> *__restrict__ a
     for (int n = 0; n < kTileTerms; n++) {
         if (n < ts.count) {
             const double v = wave_sum(acc[n]);
-            if (lane == 0) red[n][wave] = v;
+            // half sums count each pair once
+            if (lane == 0) red[n][wave] = ((ts.loop[n] >> 14) & 31u) ? 2.0 * v : v;
         }
     }
     __syncthreads();
@@ -1012,7 +1028,15 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
         std::sort(pos.begin(), pos.end());
         TileSpan sp{};
         sp.plan.n = d;
-        for (int k = 0; k < d; k++) sp.plan.low[k] = (1ULL << pos[k]) - 1ULL;
+        for (int k = 0; k < d; k++) {
+            sp.plan.low[k] = (1ULL << pos[k]) - 1ULL;
+            sp.pivots |= 1ULL << pos[k];
+        }
+        const uint64_t num_tiles = 1ULL << (N - d);
+        const int blocks = (int)std::min<uint64_t>(num_tiles, (uint64_t)expec_tile_blocks<R>(q->device));
+        sp.step = blocks;
+        for (int k = 0; k < d; k++)
+            sp.step = (sp.step & sp.plan.low[k]) | ((sp.step & ~sp.plan.low[k]) << 1);
         for (int k = 0; k < 8; k++) sp.coord[k] = coord[k];
         for (int u = 0; u < kTileRegs; u++) {
             uint64_t o = 0;
@@ -1036,8 +1060,6 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
         std::vector<int> terms;
         for (uint64_t x : chosen)
             for (int t : by_mask[x]) terms.push_back(t);
-        const uint64_t num_tiles = 1ULL << (N - d);
-        const int blocks = (int)std::min<uint64_t>(num_tiles, (uint64_t)expec_tile_blocks<R>(q->device));
         for (size_t b0 = 0; b0 < terms.size(); b0 += kTileTerms) {
             TileTermSet ts{};
             ts.count = (int)std::min<size_t>(kTileTerms, terms.size() - b0);
@@ -1048,17 +1070,16 @@ static int expec_sv_tiles(qs_qureg *q, const int *codes, const double *coeffs, i
             for (int n = 0; n < ts.count; n++) {
                 const int t = terms[b0 + n];
                 const uint32_t xc = flip_coord(xs[t]), zc = sign_coord(yzs[t]);
-                ts.xl[n] = xc & 255u;
-                ts.xh[n] = xc >> 8;
+                const uint32_t xl = xc & 255u, xh = xc >> 8;
                 ts.zl[n] = zc & 255u;
-                ts.zh[n] = zc >> 8;
                 ts.yz[n] = yzs[t];
                 // pairing of the half sums: the lowest flipped register bit,
                 // else the highest flipped thread bit
-                ts.pair[n] = -1;
-                if (ts.xh[n]) ts.pair[n] = __builtin_ctz(ts.xh[n]);
-                else if (ts.xl[n]) ts.pair[n] = 8 + (31 - __builtin_clz(ts.xl[n]));
-                if (__builtin_popcountll(xs[t] & yzs[t]) & 1) ts.kind |= 1u << n;
+                int pair = -1;
+                if (xh) pair = __builtin_ctz(xh);
+                else if (xl) pair = 8 + (31 - __builtin_clz(xl));
+                const uint32_t im = (uint32_t)(__builtin_popcountll(xs[t] & yzs[t]) & 1);
+                ts.loop[n] = xl | xh << 8 | (zc >> 8) << 11 | (uint32_t)(pair + 1) << 14 | im << 19;
                 slot_term.push_back(t);
             }
             // one block's sums are the terms' values already

@@ -67,3 +67,29 @@ def test_density_sums(qs, n, T, prec):
     assert abs(q.expec_pauli_sum(codes, coeffs) - oracle.dm_expec_pauli_sum(rho, codes, coeffs)) < tol
     assert abs(q.trace() - 1) < scalar_tol(prec) and abs(q.purity() - 1) < scalar_tol(prec)
     assert abs(q.prob_of_outcome(n - 1, 1) - oracle.dm_prob_of_outcome(rho, n - 1, 1)) < scalar_tol(prec)
+
+
+# several tiles per block; terms that pair by register bits, by thread bits and
+# not at all, alone and combined, with sums of real and of imaginary parts
+@pytest.mark.parametrize("n,prec", [(24, "c64"), (25, "c64"), (23, "c128"), (24, "c128")])
+def test_tile_sums_of_many_tiles(qs, n, prec):
+    banner(f"tile sums N={n} {prec}")
+    rng = np.random.default_rng(8900 + n)
+    rows = [np.zeros(n, int), rng.choice([0, 3], size=n)]
+    for q, c in ((0, 1), (3, 2), (2, 1)):
+        row = rng.choice([0, 3], size=n)
+        row[q] = c
+        rows.append(row)
+    masks = [rng.integers(0, 2, size=n) for _ in range(7)]
+    for x in masks + [masks[0] ^ masks[1], masks[2] ^ masks[5] ^ masks[6]]:
+        for _ in range(2):
+            rows.append(np.where(x, rng.choice([1, 2], size=n), rng.choice([0, 3], size=n)))
+    codes = np.array(rows)
+    coeffs = rng.normal(size=len(rows))
+    q = qs.Qureg(n, precision=prec).init_hashed(8901)
+    psi = q.get_amps().astype(np.complex128)
+    got = q.expec_pauli_sum(codes, coeffs)
+    # a hashed state's terms are about 2^(-n/2): complex64 products round by
+    # 2 2^-24 of sum |a_i a_j| <= 1
+    tol = 2.0 ** -22 if prec == "c64" else 1e-12
+    assert abs(got - oracle.sv_expec_pauli_sum(psi, codes, coeffs).real) <= tol * np.abs(coeffs).sum()
