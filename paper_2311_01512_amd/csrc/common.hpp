@@ -166,6 +166,11 @@ uint64_t mfma_block_cap(int k);
 // blockIdx + k gridDim, or one block per tile.
 enum { kTileGridChunk = 0, kTileGridStride = 1, kTileGridPerTile = 2 };
 int tile_grid_policy(int tile_d);
+// Blocks of one tile of 2^tile_d amplitudes each: as many as a launch can have.
+inline unsigned tile_grid_each(uint64_t tiles, int tile_d)
+{
+    return grid_for(tiles << (tile_d - kRegBits), 1 << (tile_d - kRegBits));
+}
 // Tiles per block under the chunk policy (0: as many blocks as stay resident).
 uint64_t tile_chunk();
 // Waves per SIMD that specialised tile steps are compiled for (bounds their

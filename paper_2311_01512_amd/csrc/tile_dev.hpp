@@ -47,10 +47,13 @@ __device__ __forceinline__ uint32_t tau_of(uint32_t t, const RPhase &ph)
     return c | (((t >> 4) & 1u) << ph.c4) | (((t >> 5) & 1u) << ph.c5);
 }
 
-__device__ __forceinline__ uint64_t thread_offset(uint32_t t, int lb, const RPhase &ph)
+// All thread bits at once (the offsets past the block's bits are zeros and
+// those bits of t are clear): the offsets come with one wait, not one each.
+__device__ __forceinline__ uint64_t thread_offset(uint32_t t, const RPhase &ph)
 {
     uint64_t x = 0;
-    for (int k = 0; k < lb; k++)
+#pragma unroll
+    for (int k = 0; k < kTileDimMax - kRegBits; k++)
         if ((t >> k) & 1u) x ^= ph.taddr[k];
     return x;
 }
@@ -370,6 +373,23 @@ __device__ __forceinline__ uint32_t tile_exchange(C2<R> (&x)[kRegs], unsigned ch
     return tn;
 }
 
+// Block b works on tile b, with no registers for a next one.  issued(): work
+// of the block's own while its tile is on its way.
+template <typename R, typename Plan, typename Issued, typename Phases>
+__device__ __forceinline__ void tile_once(C2<R> *__restrict__ a, const Plan &plan, const RPhase &first,
+                                          const RPhase &last, Issued issued, Phases phases)
+{
+    const uint64_t base = insert_zeros(blockIdx.x, plan), xg = thread_offset(threadIdx.x, first);
+    C2<R> x[kRegs];
+#pragma unroll
+    for (int u = 0; u < kRegs; u++) x[u] = a[base ^ xg ^ first.yaddr[u]];
+    issued();
+    phases(x, base);
+    const uint64_t xs = thread_offset(threadIdx.x, last);
+#pragma unroll
+    for (int u = 0; u < kRegs; u++) a[base ^ xs ^ last.yaddr[u]] = x[u];
+}
+
 // Blocks of 2^(d - kRegBits) threads, each walking a run of tiles: with
 // `chunk` set, block b takes the consecutive tiles b per .. b per + per - 1
 // (per = ceil(num_tiles / gridDim.x)); otherwise tiles b + k gridDim.x.  The
@@ -380,15 +400,19 @@ __device__ __forceinline__ uint32_t tile_exchange(C2<R> (&x)[kRegs], unsigned ch
 // loads are issued before the current tile's operators run (phases(x, base):
 // every phase of the step), so they are in flight during the arithmetic
 // (barriers wait for LDS only).  Tiles are disjoint, so the early read sees no
-// write of this launch.
-template <typename R, typename Phases>
-__device__ __forceinline__ void tile_walk(C2<R> *__restrict__ a, uint64_t num_tiles, const InsertPlan &plan,
-                                          const RPhase &first, const RPhase &last, int lb, bool chunk,
+// write of this launch.  issued(): work of the block's own while its first
+// tile is on its way.  TABLES: the layouts come from tables; the offsets of a
+// thread's registers, constant over the tiles, are kept from being held in 32
+// vector registers, and the bases follow by addition (a specialised step's
+// plan is constant: with an addition instead, 30 steps of width 13 on 28
+// qubits took 29.2 ms, not 27.7).
+template <typename R, bool TABLES, typename Plan, typename Issued, typename Phases>
+__device__ __forceinline__ void tile_walk(C2<R> *__restrict__ a, uint64_t num_tiles, const Plan &plan,
+                                          const RPhase &first, const RPhase &last, bool chunk, Issued issued,
                                           Phases phases)
 {
     const uint32_t t = threadIdx.x;
-    const uint64_t xg = thread_offset(t, lb, first);
-    const uint64_t xs = thread_offset(t, lb, last);
+    const uint64_t xg = thread_offset(t, first);
     const uint64_t per = chunk ? (num_tiles + gridDim.x - 1) / gridDim.x : 1;
     const uint64_t step = chunk ? 1 : gridDim.x;
     uint64_t tile = (uint64_t)blockIdx.x * per;
@@ -396,35 +420,50 @@ __device__ __forceinline__ void tile_walk(C2<R> *__restrict__ a, uint64_t num_ti
     if (end > num_tiles) end = num_tiles;
     if (tile >= end) return;
     C2<R> x[kRegs];
+    uint64_t base = insert_zeros(tile, plan), xs = 0, inc = 0;
+    if constexpr (!TABLES) xs = thread_offset(t, last);
     {
-        const uint64_t b0 = insert_zeros(tile, plan);
 #pragma unroll
-        for (int u = 0; u < kRegs; u++) x[u] = a[b0 ^ xg ^ first.yaddr[u]];
+        for (int u = 0; u < kRegs; u++) x[u] = a[base ^ xg ^ first.yaddr[u]];
+        issued();
+        if constexpr (TABLES) {
+            xs = thread_offset(t, last);
+            inc = insert_zeros(step, plan);
+        }
         // the first tile is waited for here, so that inside the loop the
         // only memory wait is for the prefetch, never for earlier stores
 #pragma unroll
         for (int u = 0; u < kRegs; u++) asm volatile("" ::"v"(x[u].x), "v"(x[u].y));
     }
     for (; tile < end; tile += step) {
-        const uint64_t base = insert_zeros(tile, plan);
-        const uint64_t next = tile + step;
-        const bool more = next < end;
+        uint64_t nb = 0;
+        if constexpr (TABLES)
+            nb = ((base | plan.pivots) + inc) & ~plan.pivots;   // carries pass over the pivots
+        else
+            base = insert_zeros(tile, plan);
         // defined on every path (zeros after the last tile): registers that
         // are undefined on one path of the loop have been given to other
         // values by the compiler's register allocation
         C2<R> nx[kRegs];
 #pragma unroll
         for (int u = 0; u < kRegs; u++) nx[u] = mk<R>(R(0), R(0));
-        if (more) {
-            const uint64_t nb = insert_zeros(next, plan);
+        if (tile + step < end) {
+            uint64_t at = xg;
+            if constexpr (TABLES)
+                asm volatile("" : "+v"(at));
+            else
+                nb = insert_zeros(tile + step, plan);
 #pragma unroll
-            for (int u = 0; u < kRegs; u++) nx[u] = a[nb ^ xg ^ first.yaddr[u]];
+            for (int u = 0; u < kRegs; u++) nx[u] = a[nb ^ at ^ first.yaddr[u]];
         }
         phases(x, base);
+        uint64_t to = xs;
+        if constexpr (TABLES) asm volatile("" : "+v"(to));
 #pragma unroll
-        for (int u = 0; u < kRegs; u++) a[base ^ xs ^ last.yaddr[u]] = x[u];
+        for (int u = 0; u < kRegs; u++) a[base ^ to ^ last.yaddr[u]] = x[u];
 #pragma unroll
         for (int u = 0; u < kRegs; u++) x[u] = nx[u];
+        base = nb;
     }
 }
 

@@ -750,10 +750,26 @@ void pack_tile_pass(const Pass &p, int precision, void *out)
 
 // ---- kernel -------------------------------------------------------------------------------
 
+// The tile's pivots as (1 << q) - 1, ascending, all ones past the last:
+// spreads a tile number over the other bits.
+struct TilePlan {
+    uint64_t low[kTileDimMax];
+    uint64_t pivots;
+};
+
+
+__device__ __forceinline__ uint64_t insert_zeros(uint64_t g, const TilePlan &p)
+{
+#pragma unroll
+    for (int k = 0; k < kTileDimMax; k++) g = (g & p.low[k]) | ((g & ~p.low[k]) << 1);
+    return g;
+}
+
 struct TileArgs {
+    RPhase first;        // the first phase, here so that a tile's addresses need no table
     int d;
     int nph;
-    InsertPlan plan;     // zeros at the tile's pivots: spreads the tile number
+    TilePlan plan;
     uint64_t num_tiles;
     int chunk;           // each block walks a run of consecutive tiles (else a stride)
     int table_lines;     // 64-byte lines of the pass's tables to warm
@@ -765,8 +781,7 @@ struct TileArgs {
 // another, each when its operator's turn comes: on a state of few tiles those
 // misses, two or three per operator, are part of the step's time (complex128
 // circuits: 60 operators on a 7-qubit density matrix 192 -> 137 us, 200 on 18
-// qubits 328 -> 313; what remains there is mostly instruction-cache misses,
-// 16 per wavefront and step).
+// qubits 328 -> 313, before the steps' other waits were shortened).
 __device__ __forceinline__ void warm_tables(const void *tables, int lines)
 {
     const uint32_t *w = reinterpret_cast<const uint32_t *>(tables);
@@ -785,28 +800,42 @@ __device__ __forceinline__ void warm_tables(const void *tables, int lines)
 constexpr int kWarmLines = 128;
 // Tiles from which the tables are not warmed: with four blocks or more per CU
 // the first ones warm them for the others (40 operators on a 12-qubit density
-// matrix in complex64, 4096 tiles: 579 us without, 597 with).
+// matrix in complex64, 4096 tiles: 490 us without, 492 with).
 constexpr uint64_t kWarmTiles = 1024;
 
 // The generic tile-step kernel: phases and operators read from the pass's
-// device tables, one switch per operator (see tile_walk).
-template <typename R>
+// device tables, one switch per operator (see tile_walk, tile_once).  On a
+// small state a step is a chain of waits: 13 us on 18 qubits in complex128,
+// of which the first tile took 4 us to arrive, each operator 0.4-0.5 (a
+// two-term gadget as long as a gate: record, jump, code and matrix each wait
+// for the one before), each exchange 0.6.  With the first phase's offsets and
+// the plan among the arguments, the offsets of all thread bits read at once
+// and the tables warmed behind the tile's loads, 10.4 us.  Registers: one tile
+// per block needs none for a next tile and no scalar spills (complex64 72
+// vector registers, complex128 98); where blocks walk, the bases follow by an
+// addition.  25 steps on 18 qubits 308 -> 260 us, 8 steps on 26 qubits in
+// complex64 2303 -> 1960 us, 6 on a 12-qubit density matrix 579 -> 490 us.
+// No gain: the next operator's code read ahead, a first round of the operators
+// over zeros to fetch their code.
+template <typename R, bool WALK>
 __global__ __launch_bounds__(1024) void k_tile_step(C2<R> *__restrict__ a, TileArgs ta, const RPhase *__restrict__ ph,
                                                      const ROp *__restrict__ ops, const C2<R> *__restrict__ mats)
 {
     extern __shared__ unsigned char lds_raw[];
-    const int lb = ta.d - kRegBits;
-    const RPhase &first = ph[0];
-    warm_tables(ph, ta.table_lines);
-    tile_walk<R>(a, ta.num_tiles, ta.plan, first, ph[ta.nph - 1], lb, ta.chunk != 0, [&](C2<R>(&x)[kRegs], uint64_t base) {
-        uint32_t tau = tau_of(threadIdx.x, first);
+    auto warm = [&] { warm_tables(ph, ta.table_lines); };
+    auto phases = [&](C2<R>(&x)[kRegs], uint64_t base) {
+        uint32_t tau = tau_of(threadIdx.x, ta.first);
         for (int p = 0; p < ta.nph; p++) {
             const RPhase &P = ph[p];
             if (p > 0) tau = tile_exchange<R>(x, lds_raw, tau, ph[p - 1], P);
             const int end = P.first_op + P.num_ops;
             for (int o = P.first_op; o < end; o++) apply_reg_op<R>(ops[o], tau, base, mats, x);
         }
-    });
+    };
+    if constexpr (WALK)
+        tile_walk<R, true>(a, ta.num_tiles, ta.plan, ta.first, ph[ta.nph - 1], ta.chunk != 0, warm, phases);
+    else
+        tile_once<R>(a, ta.plan, ta.first, ph[ta.nph - 1], warm, phases);
 }
 
 // One real sum per parametrised gadget, before the sweep applies its adjoint:
@@ -847,9 +876,11 @@ __device__ __forceinline__ double reg_grad(const C2<R> (&x)[kRegs], const C2<R> 
 // that complex128 tiles of 2^11 leave room for four blocks per CU.  A block
 // keeps a sum per gadget and wavefront over all its tiles (red, after the
 // tile).  Bound: the serial chain of a tile (operator records and matrices
-// from memory, exchanges), with 12 waves per CU in flight: 78 us per step on
-// 22 qubits in complex128 (256 MiB moved, 3.4 TB/s).  Energy and 30 gradients
-// of 45 operators there: 4.43 ms with one operator per pass, 1.00 ms so.
+// from memory, exchanges), with 12 waves per CU in flight (complex64 16):
+// about 75 us per step on 22 qubits in complex128 (256 MiB moved, 3.5 TB/s).
+// Energy and 30 gradients of 45 operators there: 4.43 ms with one operator per
+// pass, 0.91 ms so; in complex64 0.78 ms with three waves per SIMD, 0.62 with
+// the four that opaque offsets and bases by addition leave registers for.
 template <typename R>
 __global__ __launch_bounds__(512) void k_tile_adjoint(C2<R> *__restrict__ a, C2<R> *__restrict__ l, TileArgs ta,
                                                        int num_grads, const RPhase *__restrict__ ph,
@@ -863,15 +894,17 @@ __global__ __launch_bounds__(512) void k_tile_adjoint(C2<R> *__restrict__ a, C2<
     for (int i = (int)t; i < num_grads * nw; i += (int)blockDim.x) red[i] = 0.0;
     __syncthreads();
     warm_tables(ph, ta.table_lines);
-    const int lb = ta.d - kRegBits;
-    const RPhase &first = ph[0], &last = ph[ta.nph - 1];
-    const uint64_t xg = thread_offset(t, lb, first), xs = thread_offset(t, lb, last);
+    const RPhase &first = ta.first, &last = ph[ta.nph - 1];
+    const uint64_t xg = thread_offset(t, first), xs = thread_offset(t, last);
+    uint64_t base = insert_zeros(blockIdx.x, ta.plan);
+    const uint64_t inc = insert_zeros(gridDim.x, ta.plan);
     for (uint64_t tile = blockIdx.x; tile < ta.num_tiles; tile += gridDim.x) {
-        const uint64_t base = insert_zeros(tile, ta.plan);
         C2<R> x[kRegs], y[kRegs];
+        uint64_t at = xg;       // opaque: see tile_walk
+        asm volatile("" : "+v"(at));
 #pragma unroll
         for (int u = 0; u < kRegs; u++) {
-            const uint64_t i = base ^ xg ^ first.yaddr[u];
+            const uint64_t i = base ^ at ^ first.yaddr[u];
             x[u] = a[i];
             y[u] = l[i];
         }
@@ -912,6 +945,7 @@ __global__ __launch_bounds__(512) void k_tile_adjoint(C2<R> *__restrict__ a, C2<
             a[i] = x[u];
             l[i] = y[u];
         }
+        base = ((base | ta.plan.pivots) + inc) & ~ta.plan.pivots;
     }
     __syncthreads();
     for (int g = (int)t; g < num_grads; g += (int)blockDim.x) {
@@ -926,7 +960,14 @@ static TileArgs tile_args(const qs_qureg *q, const Pass &p)
     TileArgs ta{};
     ta.d = p.tile_d;
     ta.nph = (int)p.phases.size();
-    ta.plan = make_insert_plan(p.pivots);
+    ta.first = p.phases[0];
+    for (uint64_t &low : ta.plan.low) low = ~0ULL;
+    std::vector<int> pivots = p.pivots;
+    std::sort(pivots.begin(), pivots.end());
+    for (size_t k = 0; k < pivots.size(); k++) {
+        ta.plan.low[k] = (1ULL << pivots[k]) - 1ULL;
+        ta.plan.pivots |= 1ULL << pivots[k];
+    }
     ta.num_tiles = 1ULL << (q->index_bits - p.tile_d);
     if (ta.num_tiles < kWarmTiles) {
         // phases, operators and register matrices; the matrix cores'
@@ -986,11 +1027,30 @@ int launch_tile_pass(qs_qureg *q, const Pass &p, const void *dev)
         int chunk = ta.chunk;
         void *args[] = {&a, &nt, &mp, &chunk};
         const uint64_t ck = policy == kTileGridChunk ? tile_chunk() : 0;
-        const unsigned grid = policy == kTileGridPerTile ? grid_for(nt << (p.tile_d - kRegBits), block)
+        const unsigned grid = policy == kTileGridPerTile ? tile_grid_each(nt, p.tile_d)
                               : ck ? grid_for(((nt + ck - 1) / ck) * block, block)
                                    : grid_for(nt, 1, p.jit_grid);
         QS_HIP(hipModuleLaunchKernel((hipFunction_t)p.jit_fn, grid, 1, 1, block, 1, 1, p.jit_lds, q->stream, args,
                                      nullptr));
+        return QS_OK;
+    }
+    // one block per tile where a launch can have as many
+    const unsigned each = tile_grid_each(ta.num_tiles, p.tile_d);
+    const bool walk = policy != kTileGridPerTile || each != ta.num_tiles;
+    auto launch = [&](unsigned grid) {
+        if (q->precision == QS_C64) {
+            const auto kernel = walk ? k_tile_step<float, true> : k_tile_step<float, false>;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, q->stream, (float2 *)q->amps, ta, ph, ops,
+                               (const float2 *)mats);
+        } else {
+            const auto kernel = walk ? k_tile_step<double, true> : k_tile_step<double, false>;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, q->stream, (double2 *)q->amps, ta, ph, ops,
+                               (const double2 *)mats);
+        }
+    };
+    if (!walk) {
+        launch(each);
+        QS_LAUNCH_CHECK();
         return QS_OK;
     }
     // as many blocks as stay resident, so each walks many tiles
@@ -1003,23 +1063,17 @@ int launch_tile_pass(qs_qureg *q, const Pass &p, const void *dev)
         int per_cu = 0, cus = 0;
         const hipError_t e1 =
             q->precision == QS_C64
-                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tile_step<float>, (int)block, lds)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tile_step<double>, (int)block, lds);
+                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tile_step<float, true>, (int)block, lds)
+                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tile_step<double, true>, (int)block, lds);
         const hipError_t e2 = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, q->device);
         if (e1 != hipSuccess || e2 != hipSuccess || per_cu < 1 || cus < 1)
             return fail(QS_E_HIP, "occupancy query for the tile kernel failed");
         it = resident.emplace(key, per_cu * cus).first;
     }
     const uint64_t ck = policy == kTileGridChunk ? tile_chunk() : 0;
-    const unsigned grid = policy == kTileGridPerTile ? grid_for(ta.num_tiles << (p.tile_d - kRegBits), block)
-                          : ck ? grid_for(((ta.num_tiles + ck - 1) / ck) * block, block)
-                               : grid_for(ta.num_tiles, 1, (uint64_t)it->second);
-    if (q->precision == QS_C64)
-        hipLaunchKernelGGL(k_tile_step<float>, dim3(grid), dim3(block), lds, q->stream, (float2 *)q->amps, ta, ph, ops,
-                           (const float2 *)mats);
-    else
-        hipLaunchKernelGGL(k_tile_step<double>, dim3(grid), dim3(block), lds, q->stream, (double2 *)q->amps, ta, ph,
-                           ops, (const double2 *)mats);
+    launch(policy == kTileGridPerTile ? each
+           : ck ? grid_for(((ta.num_tiles + ck - 1) / ck) * block, block)
+                : grid_for(ta.num_tiles, 1, (uint64_t)it->second));
     QS_LAUNCH_CHECK();
     return QS_OK;
 }
