@@ -26,6 +26,14 @@ FLAGS = ["-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}",
          "-I", os.path.join(HERE, "..", "include")]
 
 
+# The generic tile kernels choose an operator by a switch that a whole wavefront
+# takes alike.  By default the compiler turns such branches into the chains of
+# flags that diverging lanes need (every operator then passes a dozen blocks
+# spread over 50 KiB of code, and its registers live across all of them); this
+# leaves uniform regions as they are.  200 operators on 18 qubits in complex128
+# 263 -> 247 us, 60 on 26 qubits in complex64 1974 -> 1893 us.
+FILE_FLAGS = {"tiles.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+
 RTC_HEADERS = ["dev_core.hpp", "tile_dev.hpp", "batch_dev.hpp"]   # device code compiled again at run time
 
 
@@ -58,7 +66,7 @@ SAN_LIB = os.path.join(HERE, "libqsim_asan.so")
 
 def _compile(src, san=False):
     obj = os.path.join(BUILD, os.path.basename(src) + (".san.o" if san else ".o"))
-    cmd = [HIPCC] + FLAGS + (SAN_FLAGS if san else []) + ["-I", BUILD, "-c", src, "-o", obj]
+    cmd = [HIPCC] + FLAGS + FILE_FLAGS.get(os.path.basename(src), []) + (SAN_FLAGS if san else []) + ["-I", BUILD, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")

@@ -814,7 +814,8 @@ constexpr uint64_t kWarmTiles = 1024;
 // per block needs none for a next tile and no scalar spills (complex64 72
 // vector registers, complex128 98); where blocks walk, the bases follow by an
 // addition.  25 steps on 18 qubits 308 -> 260 us, 8 steps on 26 qubits in
-// complex64 2303 -> 1960 us, 6 on a 12-qubit density matrix 579 -> 490 us.
+// complex64 2303 -> 1970 us, 6 on a 12-qubit density matrix 579 -> 495 us; with
+// the switch compiled as uniform branches 247, 1893 and 490.
 // No gain: the next operator's code read ahead, a first round of the operators
 // over zeros to fetch their code.
 template <typename R, bool WALK>
