@@ -26,13 +26,15 @@ FLAGS = ["-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}",
          "-I", os.path.join(HERE, "..", "include")]
 
 
-# The generic tile kernels choose an operator by a switch that a whole wavefront
-# takes alike.  By default the compiler turns such branches into the chains of
-# flags that diverging lanes need (every operator then passes a dozen blocks
-# spread over 50 KiB of code, and its registers live across all of them); this
-# leaves uniform regions as they are.  200 operators on 18 qubits in complex128
-# 263 -> 247 us, 60 on 26 qubits in complex64 1974 -> 1893 us.
-FILE_FLAGS = {"tiles.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+# The generic kernels of tile steps and batches choose an operator by a switch
+# that a whole wavefront takes alike, Pauli sums by tiles a term's pairing.  By default the compiler turns such
+# branches into the chains of flags that diverging lanes need (every operator
+# then passes a dozen blocks spread over 50 KiB of code, and its registers live
+# across all of them); this leaves uniform regions as they are.  200 operators
+# on 18 qubits in complex128 263 -> 247 us, 60 on 26 qubits in complex64
+# 1974 -> 1893 us; 24 circuits of 9-14 qubits with gradients 316 -> 262 us
+# (complex128 325 -> 266); 20 terms on 28 qubits 1330 -> 1270 us.
+FILE_FLAGS = {f: ["-mllvm", "-structurizecfg-skip-uniform-regions"] for f in ("tiles.hip", "batch.hip", "reduce.hip")}
 
 RTC_HEADERS = ["dev_core.hpp", "tile_dev.hpp", "batch_dev.hpp"]   # device code compiled again at run time
 
